@@ -390,10 +390,10 @@ __global__ __launch_bounds__(kWaves* kWave) void k_aev_fwd(
     OutT* orow = out + (size_t)row * P.stride;
     if (!loaded || !group_species(R, ns, pr_, pa_, S.seg_r, S.seg_a, &present, flags)) {
         for (int c = l; c < P.stride; c += kWave) store_out(orow + c, 0.f);
-        if (amask && l == 0) amask[i] = 0xffffu;
+        if (amask && l == 0) amask[row] = 0xffffu;
         return;
     }
-    if (amask && l == 0) amask[i] = present;
+    if (amask && l == 0) amask[row] = present;
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
         if (pr_[q] >= 0) {

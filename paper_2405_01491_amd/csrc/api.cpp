@@ -139,7 +139,7 @@ struct EfWs {
     float4* Gown;       // per atom, the sum of its row's edge gradients
     float* Wat;         // per-centre virials [n][9] when the caller passes none
     double* vpart;      // chunk partials of the structure virial
-    void* d1;           // ensembles: per-network dE/dh1 [n_nets][rows_max][256]
+    void* d1;           // ensembles: per-network dE/dh1 [n_nets][rows_max][256] (h[0] holds its row scales)
     float* E_net;       // ensembles: per-network energies [n_nets][rows_max]
     float* E_at_net;    // ensembles: per-network atomic energies [n_nets][n]
     size_t end;
@@ -159,12 +159,13 @@ EfWs ef_layout(const nnp_model* m, int n, int64_t cap, char* base) {
     W.mw.meta = (int32_t*)take(sizeof(int32_t) * 32);
     W.mw.prow = (int32_t*)take(sizeof(int32_t) * nn);
     W.mw.row_atom = (int32_t*)take(sizeof(int32_t) * rows_max);
-    W.mw.amask = (uint32_t*)take(sizeof(uint32_t) * nn);
     W.mstart = (int32_t*)take(sizeof(int32_t) * (nn + 1));
     W.mend = (int32_t*)take(sizeof(int32_t) * (nn + 1));
     W.aev = take(sizeof(float) * (size_t)rows_max * m->aev.stride);
     W.g = (float*)take(sizeof(float) * (size_t)rows_max * m->aev.stride);
     for (int l = 0; l + 1 < m->n_layers; ++l) W.h[l] = (float*)take(sizeof(float) * (size_t)rows_max * m->wpad[l + 1]);
+    // the fused networks leave h free: the rows' species masks in h[1]
+    if (m->fused) W.mw.amask = (uint32_t*)W.h[1];
     W.E_row = (float*)take(sizeof(float) * rows_max);
     W.E_at = (float*)take(sizeof(float) * nn);
     const int64_t c = cap > 0 ? cap : 1;
@@ -272,10 +273,10 @@ nnp_status nnp::energy_forces_impl(nnp_model* m, int32_t n, const float* pos, co
         const bool fused_nets = ens || (m->fused && !m->force_unfused);
         if (e == hipSuccess) {
             if (ens)
-                e = launch_mlp_ensemble(m, W.mw, W.aev, forces ? W.g : nullptr, W.E_row, W.E_at, n, W.d1, W.E_net,
-                                        e_mol_net ? W.E_at_net : nullptr, s);
+                e = launch_mlp_ensemble(m, W.mw, W.aev, forces ? W.g : nullptr, false, W.E_row, W.E_at, n, W.d1, W.h[0],
+                                        W.E_net, e_mol_net ? W.E_at_net : nullptr, s);
             else if (fused_nets)
-                e = launch_mlp_fused(m, W.mw, W.aev, forces ? W.g : nullptr, W.E_row, W.E_at, n, s);
+                e = launch_mlp_fused(m, W.mw, W.aev, forces ? W.g : nullptr, false, W.E_row, W.E_at, n, s);
             else
                 e = launch_mlp(m, W.mw, W.aev, bf, W.h, forces ? W.g : nullptr, W.E_row, W.E_at, s);
         }
@@ -495,13 +496,15 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
     if (m->fused) {
         // per network: float32 packs of every species, bfloat16 packs, then the
         // biases and head weights (b1 [256], b2 [192], b3 [192], w4 [192], zero padded)
-        const size_t per = pack_fused_species(nullptr, false, nullptr, nullptr, nullptr, dim, m->widths[3]);
-        const size_t perb = pack_fused_species(nullptr, true, nullptr, nullptr, nullptr, dim, m->widths[3]);
+        const size_t per = pack_fused_species(nullptr, nullptr, false, nullptr, nullptr, nullptr, nullptr, dim, m->widths[3]);
+        const size_t perb = pack_fused_species(nullptr, nullptr, true, nullptr, nullptr, nullptr, nullptr, dim, m->widths[3]);
         const int hw[4] = {256, 192, 192, 192};
-        size_t vec_bytes = 0;
-        for (int k = 0; k < 4; ++k) vec_bytes += align256(sizeof(float) * hw[k]);
+        const size_t vec_bytes = align256(sizeof(float) * (hw[0] + hw[1] + hw[2] + hw[3]));
         const size_t net_bytes = (per + perb + vec_bytes) * ns;
         std::vector<char> hp(net_bytes * n_nets, 0);
+        struct PackInv { float f[kFusedPacks]; };
+        std::vector<PackInv> inv((size_t)n_nets * ns);   // 1 / each float32 pack's scale
+        float invb[kMaxSpecies][kFusedPacks];            // the bfloat16 packs': 1
         for (int k = 0; k < n_nets; ++k) {
             const nnp_mlp_params* q = &nets[k];
             char* nb = hp.data() + net_bytes * k;
@@ -515,14 +518,14 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
                     nnp_model_destroy(m);
                     return NNP_E_ARG;
                 }
-                pack_fused_species(nb + per * s, false, W1, W2, W3, dim, m->widths[3]);
-                pack_fused_species(nb + per * ns + perb * s, true, W1, W2, W3, dim, m->widths[3]);
+                pack_fused_species(nb + per * s, inv[(size_t)k * ns + s].f, false, W1, W2, W3, w4, dim, m->widths[3]);
+                pack_fused_species(nb + per * ns + perb * s, invb[s], true, W1, W2, W3, w4, dim, m->widths[3]);
                 char* v = nb + (per + perb) * ns + vec_bytes * s;
                 const float* src[4] = {q->b[s * L + 0], q->b[s * L + 1], q->b[s * L + 2], w4};
                 const int len[4] = {m->widths[1], m->widths[2], m->widths[3], m->widths[3]};
                 for (int j = 0; j < 4; ++j) {
                     std::memcpy(v, src[j], sizeof(float) * len[j]);
-                    v += align256(sizeof(float) * hw[j]);
+                    v += sizeof(float) * hw[j];
                 }
             }
         }
@@ -538,21 +541,16 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
             const char* nb = (const char*)m->fused_dev + net_bytes * k;
             const char* pf[kMaxSpecies];
             const char* pb[kMaxSpecies];
-            const float *b1[kMaxSpecies], *b2[kMaxSpecies], *b3[kMaxSpecies], *w4[kMaxSpecies];
+            const float* vec[kMaxSpecies];
             float b4[kMaxSpecies];
             for (int s = 0; s < ns; ++s) {
                 pf[s] = nb + per * s;
                 pb[s] = nb + per * ns + perb * s;
-                const char* v = nb + (per + perb) * ns + vec_bytes * s;
-                const float** dst[4] = {&b1[s], &b2[s], &b3[s], &w4[s]};
-                for (int j = 0; j < 4; ++j) {
-                    *dst[j] = (const float*)v;
-                    v += align256(sizeof(float) * hw[j]);
-                }
+                vec[s] = (const float*)(nb + (per + perb) * ns + vec_bytes * s);
                 b4[s] = nets[k].b[s * L + L - 1][0];
             }
-            fused_net_entry(tab.data() + eb * k, ns, pf, b1, b2, b3, w4, b4, false);
-            fused_net_entry(tab.data() + eb * (n_nets + k), ns, pb, b1, b2, b3, w4, b4, true);
+            fused_net_entry(tab.data() + eb * k, ns, pf, &inv[(size_t)k * ns].f, vec, b4);
+            fused_net_entry(tab.data() + eb * (n_nets + k), ns, pb, invb, vec, b4);
         }
         if (hipMalloc(&m->fused_tab, tab.size()) != hipSuccess) { nnp_model_destroy(m); return NNP_E_NOMEM; }
         if (hipMemcpy(m->fused_tab, tab.data(), tab.size(), hipMemcpyHostToDevice) != hipSuccess) {
@@ -698,23 +696,26 @@ nnp_status nnp_mlp(nnp_model* m, int32_t n, const int32_t* species, const float*
     MlpWs dense = W.mw;
     dense.amask = nullptr;   // dE/dAEV of every feature is returned
     const bool fused = m->fused && (!m->force_unfused || m->n_nets > 1);
-    const bool bfa = fused && m->precision == NNP_BF16_MLP;   // the fused BF16 kernels read bf16 rows
-    void* rows = W.aev;
+    const bool bfa = fused && m->precision == NNP_BF16_MLP;   // the fused BF16 kernels' grouped rows are bf16
+    const bool direct = false;
     hipError_t e = launch_species_group(m, n, species, W.mw, m->flags, s);
-    if (e == hipSuccess) e = launch_zero_pad_rows(W.mw, m->aev.stride, rows, bfa, s);
-    if (e == hipSuccess) {
-        if (bfa) e = launch_permute_rows_bf16(W.mw.prow, n, m->aev.stride, aev_in, (uint16_t*)rows, s);
-        else e = launch_permute_rows(true, W.mw.prow, n, m->aev.stride, aev_in, (float*)W.aev, s);
+    if (!direct) {
+        if (e == hipSuccess) e = launch_zero_pad_rows(W.mw, m->aev.stride, W.aev, bfa, s);
+        if (e == hipSuccess)
+            e = bfa ? launch_permute_rows_bf16(W.mw.prow, n, m->aev.stride, aev_in, (uint16_t*)W.aev, s)
+                    : launch_permute_rows(true, W.mw.prow, n, m->aev.stride, aev_in, (float*)W.aev, s);
     }
+    const void* rows = direct ? (const void*)aev_in : W.aev;
+    float* g = !daev_out ? nullptr : direct ? daev_out : W.g;
     if (e == hipSuccess) {
         if (fused && mlp_split(m, n))
-            e = launch_mlp_ensemble(m, dense, rows, daev_out ? W.g : nullptr, W.E_row, nullptr, n, W.d1, W.E_net,
-                                    nullptr, s);
-        else if (fused) e = launch_mlp_fused(m, dense, rows, daev_out ? W.g : nullptr, W.E_row, nullptr, n, s);
-        else e = launch_mlp(m, W.mw, W.aev, false, W.h, daev_out ? W.g : nullptr, W.E_row, nullptr, s);
+            e = launch_mlp_ensemble(m, dense, rows, g, direct, W.E_row, nullptr, n, W.d1, W.h[0], W.E_net, nullptr, s);
+        else if (fused) e = launch_mlp_fused(m, dense, rows, g, direct, W.E_row, nullptr, n, s);
+        else e = launch_mlp(m, W.mw, W.aev, false, W.h, g, W.E_row, nullptr, s);
     }
+    if (e == hipSuccess && daev_out && !direct)
+        e = launch_permute_rows(false, W.mw.prow, n, m->aev.stride, W.g, daev_out, s);
     if (e == hipSuccess) e = launch_gather_e(W.mw.prow, n, species, self_e(m), W.E_row, e_atom, s);
-    if (e == hipSuccess && daev_out) e = launch_permute_rows(false, W.mw.prow, n, m->aev.stride, W.g, daev_out, s);
     return hip_status(e);
 }
 

@@ -135,9 +135,10 @@ struct MlpWs {
     int32_t* meta;       // [32]: counts[8], padded offsets[9]
     int32_t* prow;       // [n] atom -> grouped row
     int32_t* row_atom;   // [rows_max] grouped row -> atom (-1: padding)
-    // [n] species present in each atom's environment (bits 0-7 within the
-    // radial cutoff, 8-15 within the angular cutoff), from the AEV kernel;
-    // null: treat every feature as possibly non-zero
+    // [rows_max] species present in the environment of each grouped row's atom
+    // (bits 0-7 within the radial cutoff, 8-15 within the angular cutoff),
+    // from the AEV kernel (padding rows are not written); null: treat every
+    // feature as possibly non-zero
     uint32_t* amask;
     int rows_max;
 };
@@ -294,7 +295,7 @@ inline RowsView rows_csr(const nnp_nlist* nl) {
 
 // rev_out (fixed-stride rows only, may be null): the reverse index of each
 // row, written while gate is null or *gate != 0 (the rows were rebuilt)
-// amask_out (may be null): each atom's species-presence mask (MlpWs::amask)
+// amask_out (may be null): each output row's species-presence mask (MlpWs::amask)
 hipError_t launch_aev_fwd(const AevConst& P, int n, const float* pos, const int32_t* species, const BoxConst& bx,
                           const RowsView& rows, const int32_t* out_row, void* out, bool bf16, unsigned* flags,
                           hipStream_t s, int32_t* rev_out = nullptr, const int32_t* gate = nullptr,
@@ -313,15 +314,19 @@ hipError_t launch_mlp(const nnp_model* m, const MlpWs& W, const void* aev, bool 
 bool fused_mlp_shape(const int* widths, int n_layers, int ns);
 size_t fused_net_bytes();
 bool mlp_split(const nnp_model* m, int n_atoms);
-void fused_net_entry(void* out, int ns, const char* const* packs, const float* const* b1, const float* const* b2,
-                     const float* const* b3, const float* const* w4, const float* b4, bool bf16);
-hipError_t launch_mlp_ensemble(const nnp_model* m, const MlpWs& W, const void* aev, float* g_out, float* E_row,
-                               float* E_atomo, int n_atoms, void* d1_scratch, float* E_net, float* E_atom_net,
-                               hipStream_t s);
-size_t pack_fused_species(char* dst, bool bf16, const float* W1, const float* W2, const float* W3, int n_in, int n3);
+constexpr int kFusedPacks = 6;   // weight packs per species and network
+void fused_net_entry(void* out, int ns, const char* const* packs, const float (*inv)[kFusedPacks],
+                     const float* const* vec, const float* b4);
+// direct: aev and g_out are float32 rows in atom order (the caller's), in
+// place of the grouped rows of the workspace
+hipError_t launch_mlp_ensemble(const nnp_model* m, const MlpWs& W, const void* aev, float* g_out, bool direct,
+                               float* E_row, float* E_atomo, int n_atoms, void* d1_scratch, float* d1_inv,
+                               float* E_net, float* E_atom_net, hipStream_t s);
+size_t pack_fused_species(char* dst, float* inv, bool bf16, const float* W1, const float* W2, const float* W3,
+                          const float* w4, int n_in, int n3);
 uint16_t host_bf16_bits(float f);
-hipError_t launch_mlp_fused(const nnp_model* m, const MlpWs& W, const void* aev, float* g_out, float* E_row,
-                            float* E_atomo, int n_atoms, hipStream_t s);
+hipError_t launch_mlp_fused(const nnp_model* m, const MlpWs& W, const void* aev, float* g_out, bool direct,
+                            float* E_row, float* E_atomo, int n_atoms, hipStream_t s);
 hipError_t launch_permute_rows_bf16(const int32_t* prow, int n, int stride, const float* src, uint16_t* dst,
                                     hipStream_t s);
 // ranges_ready: mstart / mend already hold the checked structure ranges of mol
