@@ -742,6 +742,7 @@ __global__ __launch_bounds__(W* kWave) void k_rows_cells(
 // reverse index: rev[p] of i -> j is the position of i in j's sorted staging
 // row.  An absent reverse (only a clamped or truncated list can lack one)
 // points the pair at itself and raises NNP_FLAG_REVERSE.
+template <bool kHalf>
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact(
     int n, const int32_t* __restrict__ row_count, const int32_t* __restrict__ stage_col,
     const int32_t* __restrict__ stage_sh, const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col,
@@ -764,18 +765,10 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact(
         shift[3 * p + 0] = (int8_t)(sh & 0xff);
         shift[3 * p + 1] = (int8_t)((sh >> 8) & 0xff);
         shift[3 * p + 2] = (int8_t)((sh >> 16) & 0xff);
-        const int32_t* rj = stage_col + (size_t)j * kRowLds;
-        const int bj = row_ptr[j];
-        const int cj = min(row_count[j], row_ptr[j + 1] - bj);
-        int lo = 0, hi = cj;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (rj[mid] < i) lo = mid + 1; else hi = mid;
-        }
-        const bool found = lo < cj && rj[lo] == i;
-        rev[p] = found ? bj + lo : p;
-        if (!found) set_flag(flags, NNP_FLAG_REVERSE);
     }
+    const auto first = [&](int j) { return row_ptr[j]; };
+    const auto len = [&](int j) { return row_ptr[j + 1] - row_ptr[j]; };   // at most the row's count
+    if (reverse_slots<kHalf>(i, cnt, b, sc, stage_col, len, first, rev)) set_flag(flags, NNP_FLAG_REVERSE);
 }
 
 __global__ void k_fill_gated(int32_t* p, long n, int32_t v, const int32_t* gate) {
@@ -1171,7 +1164,7 @@ nnp_status build_neighbors(nnp_model* model, int32_t n, const float* pos, const 
         nl->r_list = r_list;
         nl->n_pairs = -1;
         if (n > 0)
-            k_compact<<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(
+            k_compact<false><<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(   // cut rows: not symmetric
                 n, row_count, stage_col, stage_sh, nl->row_ptr, nl->col, nl->shift, nl->rev, gate, flags);
         prof_end(model, NNP_STAGE_NEIGHBORS, s);
         return hipGetLastError() == hipSuccess ? NNP_OK : NNP_E_HIP;
@@ -1193,7 +1186,7 @@ nnp_status build_neighbors(nnp_model* model, int32_t n, const float* pos, const 
     }
     if (total > nl->capacity || total > 0x7fffffffLL) return NNP_E_CAPACITY;
     if (n > 0 && total > 0)
-        k_compact<<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(
+        k_compact<true><<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(
             n, row_count, stage_col, stage_sh, nl->row_ptr, nl->col, nl->shift, nl->rev, nullptr, flags);
     prof_end(model, NNP_STAGE_NEIGHBORS, s);
     return hipGetLastError() == hipSuccess ? NNP_OK : NNP_E_HIP;
