@@ -672,7 +672,7 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
     const int n_a = S.seg_a[ns];
     const int total = n_a * (n_a - 1) / 2;
     const float c_a = -P.eta_a * 1.44269504088896341f, m2eta_a = -2.f * P.eta_a;
-    const float zm1 = P.zeta - 1.f, l2hz = __log2f(0.5f * P.zeta);   // dF1/dw = 2^((zeta-1) log2 w + log2(zeta/2))
+    const float zm1 = P.zeta - 1.f, hz = 0.5f * P.zeta;   // dF1/dw = (zeta/2) w^(zeta-1)
     float ax_[2] = {0.f, 0.f}, ay_[2] = {0.f, 0.f}, az_[2] = {0.f, 0.f};
     // lanes per angular neighbour in the per-neighbour sums: 4 up to 16
     // neighbours, 2 up to 32, else 1 (wave-uniform)
@@ -713,16 +713,16 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
                     dF2[a] = m2eta_a * d * F2[a];
                 }
                 float Rz[kNa] = {0.f, 0.f, 0.f, 0.f};
-                float sum_c = 0.f, Ssum = 0.f;
+                float sum_c = 0.f;
                 const float us = uu * hw_rcp(sq);                 // u / sqrt(1 - u^2)
 #pragma unroll
                 for (int z = 0; z < kNz; ++z) {
-                    // base^zeta and its derivative (zeta/2) base^(zeta-1), the factor
-                    // folded into the exponent; base = 0 gives log2 = -inf and both 0
+                    // base^(zeta-1), of which base^zeta and its derivative
+                    // (zeta/2) base^(zeta-1) are multiples (an exponential
+                    // takes as long as three multiply-adds)
                     const float base = fmaxf(fmaf(uu, P.hcos_z[z], fmaf(sq, P.hsin_z[z], 0.5f)), 0.f);
-                    const float lg = hw_log2(base);
-                    const float F1 = hw_exp2(P.zeta * lg);
-                    const float dF1 = hw_exp2(fmaf(zm1, lg, l2hz));
+                    const float pw = hw_exp2(zm1 * hw_log2(base));
+                    const float F1 = base * pw;
                     const float dwdu = P.cos_z[z] - us * P.sin_z[z];
                     float Q = 0.f;
 #pragma unroll
@@ -731,12 +731,16 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
                         Q += gaz * F2[a];
                         Rz[a] += gaz * F1;
                     }
-                    sum_c += Q * dF1 * dwdu;
-                    Ssum += Q * F1;
+                    sum_c += Q * pw * dwdu;
                 }
-                float sum_r = 0.f;
+                sum_c *= hz;
+                // sum_a F2_a R_a, and with the derivative of F2_a = exp(-eta (rbar - R_a)^2)
+                float Ssum = 0.f, sum_r = 0.f;
 #pragma unroll
-                for (int a = 0; a < kNa; ++a) sum_r += Rz[a] * dF2[a];
+                for (int a = 0; a < kNa; ++a) {
+                    Ssum += Rz[a] * F2[a];
+                    sum_r += Rz[a] * dF2[a];
+                }
                 const float ff = 2.f * fj * fk;
                 const float dEdc = ff * sum_c * P.cs;
                 const float dEdrbar = ff * sum_r;
