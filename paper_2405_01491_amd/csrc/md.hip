@@ -119,12 +119,25 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
     return red[0];
 }
 
+__device__ __forceinline__ void store_noise(uint64_t seed, uint64_t step, int a, float* __restrict__ noise) {
+    float xi[3];
+    gauss3(seed, step, a, xi);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) noise[3 * a + k] = xi[k];
+}
+
+__global__ __launch_bounds__(256) void k_md_noise(int n, uint64_t seed, uint64_t step, float* __restrict__ noise) {
+    const int a = blockIdx.x * 256 + threadIdx.x;
+    if (a < n) store_noise(seed, step, a, noise);
+}
+
 template <bool kEnergy>
 __global__ __launch_bounds__(kBackThreads) void k_md_back(int n, int ne, const RowsView rows,
                                                          const int32_t* __restrict__ rev, const float4* __restrict__ G,
                                                          const float4* __restrict__ Gown, float* __restrict__ F, float* __restrict__ vel,
                                                          const float* __restrict__ inv_mass, float dt, double* ke_part,
-                                                         const MdEnergyIn E) {
+                                                         const MdEnergyIn E, int n_gather, float* __restrict__ noise,
+                                                         uint64_t noise_step, uint64_t seed) {
     __shared__ double red[kBackThreads];
     __shared__ double s_se[kMaxSpecies];
     __shared__ int last;
@@ -175,6 +188,11 @@ __global__ __launch_bounds__(kBackThreads) void k_md_back(int n, int ne, const R
             return;
         }
         blk -= ne;
+    }
+    if (blk >= n_gather) {   // the next step's noise
+        const int b = (blk - n_gather) * kBackThreads + threadIdx.x;
+        if (b < n) store_noise(seed, noise_step, b, noise);
+        return;
     }
     const int a = blk * kBackAtoms + threadIdx.x / kGatherLanes;
     const int sub = threadIdx.x % kGatherLanes;
@@ -248,16 +266,24 @@ int md_ke_parts(int n) { return ceil_div(n > 0 ? n : 1, kBackAtoms); }
 
 int md_energy_parts(int n) { return ceil_div(n > 0 ? n : 1, kEChunk); }
 
+hipError_t md_launch_noise(int n, uint64_t seed, uint64_t step, float* noise, hipStream_t s) {
+    k_md_noise<<<ceil_div(n, 256), 256, 0, s>>>(n, seed, step, noise);
+    return hipGetLastError();
+}
+
 hipError_t md_launch_back(int n, const RowsView& rows, const float4* G, const float4* Gown, float* F,
                           const MdBack& b, const MdEnergyIn* e, hipStream_t s) {
+    const int n_gather = md_ke_parts(n), n_noise = b.noise ? ceil_div(n, kBackThreads) : 0;
     if (b.fuse_energy && e) {
         const int ne = md_energy_parts(n);
         if (ne > 1 && (!e->part || !e->ticket)) return hipErrorInvalidValue;
-        k_md_back<true><<<md_ke_parts(n) + ne, kBackThreads, 0, s>>>(n, ne, rows, rows.rev, G, Gown, F, b.vel,
-                                                                     b.inv_mass, b.dt, b.ke_part, *e);
+        k_md_back<true><<<n_gather + ne + n_noise, kBackThreads, 0, s>>>(
+            n, ne, rows, rows.rev, G, Gown, F, b.vel, b.inv_mass, b.dt, b.ke_part, *e, n_gather, b.noise,
+            b.noise_step, b.seed);
     } else {
-        k_md_back<false><<<md_ke_parts(n), kBackThreads, 0, s>>>(n, 0, rows, rows.rev, G, Gown, F, b.vel,
-                                                                 b.inv_mass, b.dt, b.ke_part, MdEnergyIn{});
+        k_md_back<false><<<n_gather + n_noise, kBackThreads, 0, s>>>(
+            n, 0, rows, rows.rev, G, Gown, F, b.vel, b.inv_mass, b.dt, b.ke_part, MdEnergyIn{}, n_gather, b.noise,
+            b.noise_step, b.seed);
     }
     return hipGetLastError();
 }

@@ -37,6 +37,8 @@ struct nnp_md {
     bool fuse_front = false;  // decision and wrap inside the binning kernel (md_front_fuses)
     bool grouped = false;     // species grouping in ws_ef is current
     // device state
+    float* noise = nullptr;     // small systems' Langevin noise of step noise_step [n][3]
+    uint64_t noise_step = ~0ull;
     float *pos = nullptr, *vel = nullptr, *F = nullptr, *inv_mass = nullptr, *ref = nullptr;
     int32_t* species = nullptr;
     double* e_pot = nullptr;
@@ -106,7 +108,13 @@ nnp_status enqueue_step(nnp_md* md, uint64_t step, hipStream_t s) {
     prof_begin(m, NNP_STAGE_INTEGRATE, s);
     hipError_t e = hipSuccess;
     if (md->small) {
-        nnp_status st = launch_md_front(md->n, md->pos, md->vel, md->F, md->inv_mass, md->c, step, md->ref, cur, nxt,
+        // the last step's back kernel left this step's noise (the first step has none before it)
+        if (langevin && md->noise_step != step) {
+            e = md_launch_noise(md->n, md->c.seed, step, md->noise, s);
+            if (e != hipSuccess) return NNP_E_HIP;
+            md->noise_step = step;
+        }
+        nnp_status st = launch_md_front(md->n, md->pos, md->vel, md->F, md->inv_mass, md->c, md->noise, md->ref, cur, nxt,
                                         md->p.rebuild_every, md->trig_len, langevin, bptr, md->r_list, md->ws_nb,
                                         md->ws_nb_bytes, md->flags, s);
         if (st != NNP_OK) return st;
@@ -146,6 +154,12 @@ nnp_status enqueue_step(nnp_md* md, uint64_t step, hipStream_t s) {
     back.fuse_energy = true;
     back.e_part = md->e_part;
     back.e_ticket = md->e_ticket;
+    if (md->small && langevin) {
+        back.noise = md->noise;
+        back.noise_step = step + 1;
+        back.seed = md->c.seed;
+        md->noise_step = ~0ull;   // until the kernel that draws it is enqueued
+    }
     EfOpts opts;
     opts.skip_group = md->grouped;
     opts.md = &back;
@@ -155,6 +169,7 @@ nnp_status enqueue_step(nnp_md* md, uint64_t step, hipStream_t s) {
     st = energy_forces_impl(m, md->n, md->pos, md->species, nullptr, 1, bptr, &md->nl, md->e_pot, nullptr, md->F,
                             md->ws_ef, md->ws_ef_bytes, s, md->flags, nullptr, nullptr, &opts);
     if (st != NNP_OK) return st;
+    if (back.noise) md->noise_step = back.noise_step;
     md->grouped = true;
     if (log) {
         prof_begin(m, NNP_STAGE_INTEGRATE, s);
@@ -229,6 +244,7 @@ nnp_status nnp_md_create(nnp_model* model, int32_t n, const float* pos, const fl
     const size_t v3 = 3 * (size_t)n;
     bool ok = dmalloc(&md->pos, v3) == hipSuccess && dmalloc(&md->vel, v3) == hipSuccess &&
               dmalloc(&md->F, v3) == hipSuccess && dmalloc(&md->ref, v3) == hipSuccess &&
+              (!md->small || p.integrator != NNP_MD_LANGEVIN || dmalloc(&md->noise, v3) == hipSuccess) &&
               dmalloc(&md->inv_mass, (size_t)n) == hipSuccess && dmalloc(&md->species, (size_t)n) == hipSuccess &&
               dmalloc(&md->e_pot, 1) == hipSuccess && dmalloc(&md->st, 2) == hipSuccess &&
               dmalloc(&md->flags, 1) == hipSuccess && dmalloc(&md->ke_part, (size_t)md_ke_parts(n)) == hipSuccess &&
@@ -356,7 +372,7 @@ nnp_status nnp_md_info(nnp_md* md, nnp_md_stats* out, void* stream) {
 
 void nnp_md_destroy(nnp_md* md) {
     if (!md) return;
-    void* bufs[] = {md->pos, md->vel, md->F, md->ref, md->inv_mass, md->species, md->e_pot, md->st, md->flags,
+    void* bufs[] = {md->pos, md->vel, md->F, md->noise, md->ref, md->inv_mass, md->species, md->e_pot, md->st, md->flags,
                     md->ke_part, md->d2_part, md->e_part, md->e_ticket, md->log, md->nl.rev, md->ws_ef, md->ws_nb};
     for (void* b : bufs)
         if (b) (void)hipFree(b);

@@ -70,13 +70,16 @@ __device__ __forceinline__ void gauss3(uint64_t seed, uint64_t step, int a, floa
 // flags the coordinates).  md_first_load reads what the step needs, so that
 // a thread with several atoms can issue every load before the first use;
 // md_first_finish computes and stores.
+// noise: the step's Gaussian numbers [n][3] where an earlier kernel left them
+// (the last of the step before), else null and each atom draws its own.
 struct MdAtomIn {
-    float im, v[3], f[3], x[3], r[3];
+    float im, v[3], f[3], x[3], r[3], xi[3];
 };
 
 __device__ __forceinline__ MdAtomIn md_first_load(int a, const float* __restrict__ pos,
                                                   const float* __restrict__ vel, const float* __restrict__ F,
-                                                  const float* __restrict__ inv_mass, const float* __restrict__ ref) {
+                                                  const float* __restrict__ inv_mass, const float* __restrict__ ref,
+                                                  const float* __restrict__ noise = nullptr) {
     MdAtomIn q;
     q.im = inv_mass[a];
 #pragma unroll
@@ -85,11 +88,12 @@ __device__ __forceinline__ MdAtomIn md_first_load(int a, const float* __restrict
         q.f[k] = F[3 * a + k];
         q.x[k] = pos[3 * a + k];
         q.r[k] = ref[3 * a + k];
+        if (noise) q.xi[k] = noise[3 * a + k];
     }
     return q;
 }
 
-template <bool kLangevin>
+template <bool kLangevin, bool kNoise = false>
 __device__ __forceinline__ float md_first_finish(int a, const MdAtomIn& q, float* __restrict__ pos,
                                                  float* __restrict__ vel, const MdStepConst& c, uint64_t step,
                                                  float* xout = nullptr) {
@@ -101,8 +105,8 @@ __device__ __forceinline__ float md_first_finish(int a, const MdAtomIn& q, float
         x[k] = q.x[k];
     }
     if (kLangevin) {
-        float xi[3];
-        gauss3(c.seed, step, a, xi);
+        float xi[3] = {q.xi[0], q.xi[1], q.xi[2]};
+        if (!kNoise) gauss3(c.seed, step, a, xi);
         const float sig = c.c2 * sqrtf(c.kT * kAccUnit * q.im);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -226,7 +230,14 @@ struct MdBack {
     bool fuse_energy;         // sum the structure energy in the same kernel
     double* e_part;           // [md_energy_parts(n)] chunk sums of the structure energy
     unsigned* e_ticket;       // one word, zero between launches
+    // small systems' Langevin steps: the next step's noise [n][3] (or null),
+    // by blocks of this kernel that have no other work, so that the front
+    // kernel's one workgroup does not draw it for every atom
+    float* noise;
+    uint64_t noise_step, seed;
 };
+// noise [n][3] of one step
+hipError_t md_launch_noise(int n, uint64_t seed, uint64_t step, float* noise, hipStream_t s);
 
 // d2_part: [2 md_first_parts(n)] per-block two largest squared displacements
 int md_first_parts(int n);
@@ -242,7 +253,7 @@ hipError_t md_launch_back(int n, const RowsView& rows, const float4* G, const fl
 // neighbors.hip: the fused front of a step for small systems
 bool md_front_fits(int n, const float* box_host, float r_list);
 nnp_status launch_md_front(int n, float* pos, float* vel, const float* F, const float* inv_mass, const MdStepConst& c,
-                           uint64_t step, float* ref, const MdState* cur, MdState* nxt, int rebuild_every,
+                           const float* noise, float* ref, const MdState* cur, MdState* nxt, int rebuild_every,
                            float trig_len, bool langevin, const float* box_host, float r_list, void* ws,
                            size_t ws_bytes, unsigned* flags, hipStream_t s);
 // neighbors.hip: whether build_neighbors can take an MdFront (the binning

@@ -795,8 +795,8 @@ static_assert(kFrontPer % kFrontBatch == 0, "whole batches of atoms per thread")
 template <bool kLangevin>
 __global__ __launch_bounds__(kFrontThreads) void k_md_front(
     int n, float* __restrict__ pos, float* __restrict__ vel, const float* __restrict__ F,
-    const float* __restrict__ inv_mass, const MdStepConst c, uint64_t step, float* __restrict__ ref,
-    const MdState* cur_st, MdState* nxt, int rebuild_every, float trig_len, const Grid g, int n_cells,
+    const float* __restrict__ inv_mass, const MdStepConst c, const float* __restrict__ noise,
+    float* __restrict__ ref, const MdState* cur_st, MdState* nxt, int rebuild_every, float trig_len, const Grid g, int n_cells,
     int32_t* __restrict__ cell_of,
     int32_t* __restrict__ cell_start, int32_t* __restrict__ cell_atoms, unsigned* flags) {
     __shared__ int s_cnt[kFrontCells + 1];
@@ -815,12 +815,12 @@ __global__ __launch_bounds__(kFrontThreads) void k_md_front(
 #pragma unroll
         for (int u = 0; u < kFrontBatch; ++u) {
             const int a = t + (k0 + u) * kFrontThreads;
-            if (a < n) in[u] = md_first_load(a, pos, vel, F, inv_mass, ref);
+            if (a < n) in[u] = md_first_load(a, pos, vel, F, inv_mass, ref, kLangevin ? noise : nullptr);
         }
 #pragma unroll
         for (int u = 0; u < kFrontBatch; ++u) {
             const int a = t + (k0 + u) * kFrontThreads;
-            if (a < n) top2_add(m1, m2, md_first_finish<kLangevin>(a, in[u], pos, vel, c, step, xs[k0 + u]));
+            if (a < n) top2_add(m1, m2, md_first_finish<kLangevin, true>(a, in[u], pos, vel, c, 0, xs[k0 + u]));
         }
     }
     top2_wave(m1, m2);
@@ -1002,7 +1002,7 @@ bool md_front_fits(int n, const float* box_host, float r_list) {
 }
 
 nnp_status launch_md_front(int n, float* pos, float* vel, const float* F, const float* inv_mass, const MdStepConst& c,
-                           uint64_t step, float* ref, const MdState* cur, MdState* nxt, int rebuild_every,
+                           const float* noise, float* ref, const MdState* cur, MdState* nxt, int rebuild_every,
                            float trig_len, bool langevin, const float* box_host, float r_list, void* ws,
                            size_t ws_bytes, unsigned* flags, hipStream_t s) {
     Grid g;
@@ -1017,11 +1017,11 @@ nnp_status launch_md_front(int n, float* pos, float* vel, const float* F, const 
     int32_t* cell_start = (int32_t*)(base + L.cell_start);
     int32_t* cell_atoms = (int32_t*)(base + L.cell_atoms);
     if (langevin)
-        k_md_front<true><<<1, kFrontThreads, 0, s>>>(n, pos, vel, F, inv_mass, c, step, ref, cur, nxt,
+        k_md_front<true><<<1, kFrontThreads, 0, s>>>(n, pos, vel, F, inv_mass, c, noise, ref, cur, nxt,
                                                      rebuild_every, trig_len, g, (int)n_cells, cell_of, cell_start,
                                                      cell_atoms, flags);
     else
-        k_md_front<false><<<1, kFrontThreads, 0, s>>>(n, pos, vel, F, inv_mass, c, step, ref, cur, nxt,
+        k_md_front<false><<<1, kFrontThreads, 0, s>>>(n, pos, vel, F, inv_mass, c, noise, ref, cur, nxt,
                                                       rebuild_every, trig_len, g, (int)n_cells, cell_of, cell_start,
                                                       cell_atoms, flags);
     return hipGetLastError() == hipSuccess ? NNP_OK : NNP_E_HIP;
