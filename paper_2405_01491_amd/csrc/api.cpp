@@ -292,10 +292,11 @@ nnp_status nnp::energy_forces_impl(nnp_model* m, int32_t n, const float* pos, co
             if (e == hipSuccess)
                 e = launch_energy(n, n_mol, mol, species, self_e(m), ms, me, given, W.mw, W.E_at, e_mol, e_atom,
                                   flags, s);
-            // ensembles: every network's structure energies (self energies included)
-            for (int k = 0; e_mol_net && k < m->n_nets && e == hipSuccess && n > 0; ++k)
-                e = launch_energy(n, n_mol, mol, species, self_e(m), ms, me, true, W.mw, W.E_at_net + (size_t)k * n,
-                                  e_mol_net + (size_t)k * n_mol, nullptr, flags, s);
+            // ensembles: every network's structure energies (self energies
+            // included), all in one pass; the networks are done with d1
+            if (e_mol_net && e == hipSuccess && n > 0)
+                e = launch_energy(n, n_mol, mol, species, self_e(m), ms, me, true, W.mw, W.E_at_net, e_mol_net,
+                                  nullptr, flags, s, m->n_nets, (double*)W.d1);
         }
         pend(NNP_STAGE_ENERGY);
     }

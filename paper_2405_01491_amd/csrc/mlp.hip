@@ -383,9 +383,11 @@ __global__ __launch_bounds__(256) void k_head(const int32_t* meta, int ns, const
 // are added in float64 per atom.  Atoms without a network energy (invalid
 // species, flagged) contribute zero.
 template <int kThreads>
-__global__ __launch_bounds__(kThreads) void k_energy(int n_mol, const int32_t* mstart, const int32_t* mend,
+__global__ __launch_bounds__(kThreads) void k_energy(int n_atoms, int n_mol, const int32_t* mstart, const int32_t* mend,
                                                     const int32_t* prow, const int32_t* species, const SelfE se,
                                                     const float* E_at, double* e_mol, float* e_atom) {
+    E_at += (size_t)blockIdx.y * n_atoms;   // the y-th network's
+    e_mol += (size_t)blockIdx.y * n_mol;
     __shared__ double part[kThreads];
     const int m = blockIdx.x;
     if (m >= n_mol) return;
@@ -413,6 +415,8 @@ constexpr int kChunk = 4096;
 __global__ __launch_bounds__(1024) void k_energy_chunks(int n, const int32_t* prow, const int32_t* species,
                                                        const SelfE se, const float* E_at, double* part,
                                                        float* e_atom) {
+    E_at += (size_t)blockIdx.y * n;   // the y-th network's
+    part += (size_t)blockIdx.y * gridDim.x;
     __shared__ double red[1024];
     const int base = blockIdx.x * kChunk;
     double acc = 0.0;
@@ -435,6 +439,8 @@ __global__ __launch_bounds__(1024) void k_energy_chunks(int n, const int32_t* pr
 }
 
 __global__ __launch_bounds__(256) void k_energy_final(int nparts, const double* part, double* e_mol) {
+    part += (size_t)blockIdx.y * nparts;
+    e_mol += blockIdx.y;
     __shared__ double red[256];
     double acc = 0.0;
     for (int q = threadIdx.x; q < nparts; q += 256) acc += part[q];
@@ -450,6 +456,8 @@ __global__ __launch_bounds__(256) void k_energy_final(int nparts, const double* 
 __global__ __launch_bounds__(1024) void k_energy_single(int n, const int32_t* prow, const int32_t* species,
                                                        const SelfE se, const float* E_at, double* e_mol,
                                                        float* e_atom) {
+    E_at += (size_t)blockIdx.y * n;   // the y-th network's
+    e_mol += blockIdx.y;
     __shared__ double red[1024];
     double acc = 0.0;
     for (int a = threadIdx.x; a < n; a += 1024) {
@@ -630,18 +638,19 @@ hipError_t launch_mlp(const nnp_model* m, const MlpWs& W, const void* aev, bool 
 
 hipError_t launch_energy(int n, int n_mol, const int32_t* mol, const int32_t* species, const SelfE& se,
                          int32_t* mstart, int32_t* mend, bool ranges_ready, const MlpWs& W, const float* E_at,
-                         double* e_mol, float* e_atom, unsigned* flags, hipStream_t s) {
+                         double* e_mol, float* e_atom, unsigned* flags, hipStream_t s, int n_sets, double* parts) {
     if (n_mol == 1 && !mol && n <= 2 * kChunk) {
-        k_energy_single<<<1, 1024, 0, s>>>(n, W.prow, species, se, E_at, e_mol, e_atom);
+        k_energy_single<<<dim3(1, n_sets), 1024, 0, s>>>(n, W.prow, species, se, E_at, e_mol, e_atom);
         return hipGetLastError();
     }
     if (n_mol == 1 && n > 2 * kChunk) {
         // mol must still be validated: a single structure means every mol entry is 0
         if (mol && !ranges_ready) k_mol_ranges2<<<ceil_div(n, 256), 256, 0, s>>>(mol, n, n_mol, mstart, mend, flags);
         const int nparts = ceil_div(n, kChunk);
-        double* part = (double*)W.bcount;   // >= nparts doubles: bcount holds 8 ints per 1024 atoms
-        k_energy_chunks<<<nparts, 1024, 0, s>>>(n, W.prow, species, se, E_at, part, e_atom);
-        k_energy_final<<<1, 256, 0, s>>>(nparts, part, e_mol);
+        // one set: bcount holds >= nparts doubles (8 ints per 1024 atoms)
+        double* part = parts ? parts : (double*)W.bcount;
+        k_energy_chunks<<<dim3(nparts, n_sets), 1024, 0, s>>>(n, W.prow, species, se, E_at, part, e_atom);
+        k_energy_final<<<dim3(1, n_sets), 256, 0, s>>>(nparts, part, e_mol);
         return hipGetLastError();
     }
     if (n_mol > 0) {
@@ -655,9 +664,9 @@ hipError_t launch_energy(int n, int n_mol, const int32_t* mol, const int32_t* sp
             if (n > 0) k_mol_ranges2<<<ceil_div(n, 256), 256, 0, s>>>(mol, n, n_mol, mstart, mend, flags);
         }
         if (n_mol == 1)
-            k_energy<1024><<<1, 1024, 0, s>>>(n_mol, mstart, mend, W.prow, species, se, E_at, e_mol, e_atom);
+            k_energy<1024><<<dim3(1, n_sets), 1024, 0, s>>>(n, n_mol, mstart, mend, W.prow, species, se, E_at, e_mol, e_atom);
         else
-            k_energy<128><<<n_mol, 128, 0, s>>>(n_mol, mstart, mend, W.prow, species, se, E_at, e_mol, e_atom);
+            k_energy<128><<<dim3(n_mol, n_sets), 128, 0, s>>>(n, n_mol, mstart, mend, W.prow, species, se, E_at, e_mol, e_atom);
     } else if (e_atom && n > 0) {
         k_atom_e<<<ceil_div(n, 256), 256, 0, s>>>(W.prow, n, species, se, E_at, e_atom);
     }

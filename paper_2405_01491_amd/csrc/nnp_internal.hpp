@@ -410,9 +410,13 @@ hipError_t launch_mlp_fused(const nnp_model* m, const MlpWs& W, const void* aev,
 hipError_t launch_permute_rows_bf16(const int32_t* prow, int n, int stride, const float* src, uint16_t* dst,
                                     hipStream_t s);
 // ranges_ready: mstart / mend already hold the checked structure ranges of mol
+// n_sets > 1: as many sets of network energies [n_sets][n] summed in the same
+// launches into e_mol [n_sets][n_mol] (e_atom null; parts: scratch of n_sets
+// doubles per 4,096 atoms)
 hipError_t launch_energy(int n, int n_mol, const int32_t* mol, const int32_t* species, const SelfE& se,
                          int32_t* mstart, int32_t* mend, bool ranges_ready, const MlpWs& W, const float* E_at,
-                         double* e_mol, float* e_atom, unsigned* flags, hipStream_t s);
+                         double* e_mol, float* e_atom, unsigned* flags, hipStream_t s, int n_sets = 1,
+                         double* parts = nullptr);
 hipError_t launch_permute_rows(bool to_grouped, const int32_t* prow, int n, int stride, const float* src, float* dst,
                                hipStream_t s);
 hipError_t launch_gather_e(const int32_t* prow, int n, const int32_t* species, const SelfE& se, const float* E_row,
