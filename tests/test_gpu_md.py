@@ -145,6 +145,30 @@ def test_engine_langevin_tracks_oracle(spec_bias, precision):
     assert dx < 1e-4 * tol and dv < 1e-5 * tol
 
 
+@pytest.mark.parametrize("n_mol", [86, 190])
+def test_engine_langevin_noise_of_several_blocks(spec_bias, n_mol):
+    """Small systems' noise is drawn a step ahead, 256 atoms a block: 258 and
+    570 atoms, against the oracle's noise; then a run cut at every step."""
+    w = synthetic.geometry.small_water_box(n_mol)
+    model = nnp.Model(spec_bias, "fp32")
+    masses = synthetic.MASSES[w.species]
+    v0 = nmd.maxwell_boltzmann(masses, 300.0, seed=8)
+    kw = dict(dt=0.5, integrator="langevin", temperature=300.0, friction=20.0, seed=78, skin=0.5, rebuild_every=2)
+    eng = _engine(model, w, v0, **kw)
+    eng.run(3)
+    x, v, _, _ = [t.cpu().numpy() for t in eng.state()]
+    nl = oracle.neighbor_list(w.pos, None, w.box, 5.6)
+    xr, vr, _ = oracle.langevin_baoab(
+        w.pos, v0, masses, lambda y: oracle.energy_forces_f64(y, w.species, w.box, spec_bias, nl),
+        0.5, 3, 300.0, 20.0, seed=78)
+    assert np.abs(_min_image(x - xr, w.box)).max() < 1e-4 and np.abs(v - vr).max() < 1e-5
+    cut = _engine(model, w, v0, **kw)
+    for _ in range(3):
+        cut.run(1)
+    for a, b in zip(eng.state(), cut.state()):
+        assert torch.equal(a, b)
+
+
 def test_engine_split_runs_are_exact(spec):
     """A run cut into pieces gives bit-for-bit the state of one run of the
     same length: the noise is keyed by (step, atom), the rebuild decision and

@@ -146,3 +146,21 @@ def test_empty_system(model):
     pos = torch.zeros((0, 3), dtype=torch.float32, device=dev())
     nl = nnp.nnp_neighbors(model, pos, None, 1, np.array([12.0, 12, 12], np.float32), 5.1)
     assert nl.n_pairs == 0
+
+
+@pytest.mark.parametrize("m", [2, 17, 18, 33, 64, 65, 66, 81, 129, 256, 257])
+def test_reverse_index_at_row_lengths(model, m):
+    """Structures of m atoms that are all neighbours (rows of m - 1 entries):
+    the reverse search takes 16 entries a block, four blocks at once and one at
+    a time beyond 64, up to the longest row of 256; three structures, so that
+    the atoms' numbers are not their places."""
+    rng = np.random.default_rng(m)
+    pos = rng.normal(size=(3, m, 3))
+    pos *= (2.5 * rng.random((3, m, 1)) ** (1 / 3)) / np.linalg.norm(pos, axis=2, keepdims=True)
+    mol = np.repeat(np.arange(3, dtype=np.int32), m)
+    w = types.SimpleNamespace(name="balls_%d" % m, pos=pos.reshape(-1, 3).astype(np.float32), mol=mol, n_mol=3,
+                              species=np.zeros(3 * m, np.int32), box=None, n_atoms=3 * m)
+    p, _, mo = to_dev(w)
+    nl = nnp.nnp_neighbors(model, p, mo, 3, None, 5.1)
+    assert nl.n_pairs == 3 * m * (m - 1)
+    _check_list(nl, w, 5.1)
