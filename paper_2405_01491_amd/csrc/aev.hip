@@ -325,62 +325,34 @@ __global__ __launch_bounds__(kWaves* kWave) void k_aev_fwd(
     __shared__ FwdLds lds[kWaves];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // wave-uniform: the atom is a scalar
     const int l = lane_id();
-    const int i = blockIdx.x * kWaves + w;
+    const int n_fwd = (n + kWaves - 1) / kWaves;
+    const bool reverse = kPacked && (int)blockIdx.x >= n_fwd;
+    const int i = ((int)blockIdx.x - (reverse ? n_fwd : 0)) * kWaves + w;
     if (i >= n) return;
-    FwdLds& S = lds[w];
-    // the row's extent and grouped row, loaded ahead of the rebuild gate
-    const int rb = rows.begin(i), re = rows.end(i);
-    const int row = out_row ? out_row[i] : i;
-    // fixed-stride rows just rebuilt: the reverse index, found once per
-    // unordered pair by the row of its lower index.  For a pair i -> j with
-    // j > i, i's slot q in the row of j is found by bisection (rows are
-    // sorted by neighbour) and both rev[p] = q and rev[q] = p are written;
-    // the pairs with j < i are written by the row of j.  A lane searches the
-    // rows of its pairs p and p + 64 side by side, so that the dependent
-    // loads of the two searches are in flight together; a finished search
-    // issues no load.  A pair i -> j, j > i, whose reverse is absent is
+    // Fixed-stride rows just rebuilt: blocks after the features' (only then
+    // launched; gated like the rebuild) find the reverse index, which nothing
+    // here reads, once per unordered pair, by the row of its lower index.  In
+    // the features' own waves the search stood before everything else, up to
+    // eight dependent reads (bisection) on a chip that few atoms leave idle;
+    // beside them, us on a rebuild step, before and after: 23.8 -> 21.6 at
+    // 4,500 atoms, 37.5 -> 32.3 at 9,000, 85.6 -> 81.0 at 30,000, 313 -> 313 at
+    // 99,999; without a rebuild the same.  Alternating with the features'
+    // blocks: 29.8 at 4,500, 410 at 99,999.  A pair whose reverse is absent is
     // flagged and left pointing at itself.  (The builder's lists are
     // symmetric; only a row emptied for overflowing, which is flagged on its
     // own, leaves a slot of another row unresolved.)
-    if (rev_out && (!gate || *gate)) {
-        const int b = rb, e = re;
-        bool missing = false;
-        for (int p0 = b + l; p0 < e; p0 += 2 * kWave) {
-            const int p1 = p0 + kWave;
-            const bool two = p1 < e;
-            const int j0 = rows.col[p0];
-            const int j1 = two ? rows.col[p1] : j0;
-            const bool s0 = j0 > i, s1 = two && j1 > i;
-            const int e0 = rows.end(j0), e1 = two ? rows.end(j1) : e0;
-            int lo0 = rows.begin(j0), hi0 = s0 ? e0 : lo0;
-            int lo1 = rows.begin(j1), hi1 = s1 ? e1 : lo1;
-            while (lo0 < hi0 || lo1 < hi1) {
-                const int m0 = (lo0 + hi0) >> 1, m1 = (lo1 + hi1) >> 1;
-                int c0 = 0, c1 = 0;
-                if (lo0 < hi0) c0 = rows.col[m0];
-                if (lo1 < hi1) c1 = rows.col[m1];
-                if (lo0 < hi0) {
-                    if (c0 < i) lo0 = m0 + 1; else hi0 = m0;
-                }
-                if (lo1 < hi1) {
-                    if (c1 < i) lo1 = m1 + 1; else hi1 = m1;
-                }
-            }
-            if (s0) {
-                const bool f0 = lo0 < e0 && rows.col[lo0] == i;
-                rev_out[p0] = f0 ? lo0 : p0;
-                if (f0) rev_out[lo0] = p0;
-                missing |= !f0;
-            }
-            if (s1) {
-                const bool f1 = lo1 < e1 && rows.col[lo1] == i;
-                rev_out[p1] = f1 ? lo1 : p1;
-                if (f1) rev_out[lo1] = p1;
-                missing |= !f1;
-            }
-        }
-        if (missing) set_flag(flags, NNP_FLAG_REVERSE);
+    if (reverse) {
+        if (gate && !*gate) return;
+        const int b = rows.begin(i);
+        const auto first = [&](int j) { return rows.begin(j); };
+        const auto len = [&](int j) { return rows.end(j) - rows.begin(j); };
+        if (reverse_slots<true>(i, rows.end(i) - b, b, rows.col + b, rows.col, len, first, rev_out))
+            set_flag(flags, NNP_FLAG_REVERSE);
+        return;
     }
+    FwdLds& S = lds[w];
+    const int rb = rows.begin(i), re = rows.end(i);
+    const int row = out_row ? out_row[i] : i;
     const int ns = P.ns;
     Row R;
     int pr_[kQ], pa_[kQ];
@@ -858,8 +830,9 @@ hipError_t launch_aev_fwd(const AevConst& P, int n, const float* pos, const int3
                           const RowsView& rows, const int32_t* out_row, void* out, bool bf16, unsigned* flags,
                           hipStream_t s, int32_t* rev_out, const int32_t* gate, uint32_t* amask_out) {
     if (n <= 0) return hipSuccess;
-    const int grid = ceil_div(n, kWaves);
     const bool packed = rows.row_ptr == nullptr;
+    if (rev_out && !packed) return hipErrorInvalidValue;   // the search reads fixed-stride rows
+    const int grid = ceil_div(n, kWaves) * (rev_out ? 2 : 1);
 #define NNP_AEV_FWD(T, PK) \
     k_aev_fwd<T, PK><<<grid, kWaves * kWave, 0, s>>>(P, n, pos, species, bx, rows, out_row, (T*)out, flags, rev_out, \
                                                      gate, amask_out)
