@@ -292,7 +292,9 @@ __device__ __forceinline__ float3 gather_row_force(const RowsView& rows, const i
 // lane that finds i writes (rows of more than 64 entries go on in steps of
 // 64).  Two dependent reads where a bisection by one lane has six to eight, and
 // a third of the instructions of sixteen lanes reading 64 entries at once:
-// k_compact at 99,999 atoms 128 us (bisection), 95 (sixteen lanes), 74.
+// k_compact at 99,999 atoms 128 us (bisection), 95 (sixteen lanes), 74; at
+// 1,500 atoms, where the launch is latency and instruction fetch, 5.5 and 6.2
+// (three or four times kRows at once: 5.8-6.3, and 70-77 at 99,999).
 // kHalf: only the neighbours j > i, both slots written, in lists that are
 // symmetric; else each row writes its own slots.  A neighbour without i leaves
 // the slot pointing at itself.  Returns whether that occurred on this lane.
