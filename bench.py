@@ -457,11 +457,11 @@ def roofline_of(dom, stages, w, spec, precision, model, nets, n_pairs, traffic_p
         flop, dense_flop, feats = (fwd + adj) * nets * N, (fwd + adj) * nets * N, float(spec.aev_dim)
         if model.fused_mlp:
             flop, dense_flop, feats = mlp_useful_flops(w, spec, precision, nets)
-        # the fused FP32 form multiplies float16 pairs: three products at the
+        # the fused FP32 form multiplies float16 parts: four products at the
         # bfloat16 / float16 rate for each float32 one
         peak = MI355X_PEAK["fp32_TFLOPs"]
         if precision == "bf16" or model.fused_mlp:
-            peak = MI355X_PEAK["bf16_TFLOPs"] / (1 if precision == "bf16" else 3)
+            peak = MI355X_PEAK["bf16_TFLOPs"] / (1 if precision == "bf16" else 4)
         achieved = flop / (avg_ms * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": None, "stage": "mlp (per-species networks, forward + adjoint)",

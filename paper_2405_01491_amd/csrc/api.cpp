@@ -497,8 +497,8 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
     if (m->fused) {
         // per network: float32 packs of every species, bfloat16 packs, then the
         // biases and head weights (b1 [256], b2 [192], b3 [192], w4 [192], zero padded)
-        const size_t per = pack_fused_species(nullptr, nullptr, false, nullptr, nullptr, nullptr, nullptr, dim, m->widths[3]);
-        const size_t perb = pack_fused_species(nullptr, nullptr, true, nullptr, nullptr, nullptr, nullptr, dim, m->widths[3]);
+        const size_t per = pack_fused_species(nullptr, nullptr, false, nullptr, nullptr, nullptr, dim, m->widths[3]);
+        const size_t perb = pack_fused_species(nullptr, nullptr, true, nullptr, nullptr, nullptr, dim, m->widths[3]);
         const int hw[4] = {256, 192, 192, 192};
         const size_t vec_bytes = align256(sizeof(float) * (hw[0] + hw[1] + hw[2] + hw[3]));
         const size_t net_bytes = (per + perb + vec_bytes) * ns;
@@ -519,8 +519,8 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
                     nnp_model_destroy(m);
                     return NNP_E_ARG;
                 }
-                pack_fused_species(nb + per * s, inv[(size_t)k * ns + s].f, false, W1, W2, W3, w4, dim, m->widths[3]);
-                pack_fused_species(nb + per * ns + perb * s, invb[s], true, W1, W2, W3, w4, dim, m->widths[3]);
+                pack_fused_species(nb + per * s, inv[(size_t)k * ns + s].f, false, W1, W2, W3, dim, m->widths[3]);
+                pack_fused_species(nb + per * ns + perb * s, invb[s], true, W1, W2, W3, dim, m->widths[3]);
                 char* v = nb + (per + perb) * ns + vec_bytes * s;
                 const float* src[4] = {q->b[s * L + 0], q->b[s * L + 1], q->b[s * L + 2], w4};
                 const int len[4] = {m->widths[1], m->widths[2], m->widths[3], m->widths[3]};

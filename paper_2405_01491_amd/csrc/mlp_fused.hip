@@ -23,18 +23,26 @@
 //
 //   BF16 form: v_mfma_f32_16x16x32_bf16, inputs rounded to bfloat16, float32
 //     accumulation.
-//   FP32 form: v_mfma_f32_16x16x32_f16 on inputs split into two float16
-//     numbers, x s = hi + lo with s a power of two (hi the nearest float16 of
-//     x s, lo that of the remainder), and three products per step,
-//     lo*hi + hi*lo + hi*hi, into float32 accumulators.  s is taken per
-//     product from the largest magnitude: for an atom's input row, measured
-//     each time, and for a species' weight matrix, once when it is packed; the
-//     largest element then lies in [2^14, 2^15), elements down to 2^-17 of it
-//     keep both parts in full (22 to 24 bits) and smaller ones are off by at
-//     most 2^-40 of it.  One step replaces eight v_mfma_f32_16x16x4_f32 (256
-//     cycles) by three products of 16 cycles, and rounds a sum three times
-//     where that rounded 32 times: on random operands the error of a product
-//     against 64 bits is 0.65 of the float32 MFMA's at K = 128, 256 and 1024.
+//   FP32 form: v_mfma_f32_16x16x32_f16 on inputs split into float16 numbers,
+//     x s = hi + lo with s a power of two (hi the nearest float16 of x s, lo
+//     that of the remainder); weights also keep what hi + lo leaves, so that
+//     all of their 24 bits count.  Four products per step, rest*hi + lo*hi +
+//     hi*lo + hi*hi, into float32 accumulators.  s is taken per product from
+//     the largest magnitude: for an atom's input row, measured each time, and
+//     for a species' weight matrix, once when it is packed; the largest element
+//     then lies in [2^14, 2^15).  Weights down to 2^-15 of it are whole, and
+//     smaller ones off by at most 2^-39 of it; inputs down to 2^-17 of the
+//     largest keep 22 to 24 bits, smaller ones are off by at most 2^-39 of it.
+//     One step replaces eight v_mfma_f32_16x16x4_f32 (256 cycles) by four
+//     products of 16 cycles, and rounds a sum four times where that rounded 32
+//     times.  Error (rms) against 64 bits over six sets of weights (uniform,
+//     normal, heavy-tailed, biased), water and organic boxes, beside the float32
+//     MFMAs': atomic energies 3.0e-8 of their terms (4.3e-8), the mean of a
+//     species' energies 4.4e-9 (4.3e-9; largest 1.0e-8, 1.3e-8), a box's energy
+//     3.0e-9 (3.2e-9), dE/dAEV 3.0e-7 (4.7e-7), its sum over a box 0.7e-7
+//     (1.3e-7); over ten sets, a box's virial 3.3e-8 of its atoms' (6.3e-8).
+//     The fourth product takes a quarter more time: 184 and 226 us at 99,999
+//     water atoms, 57 and 72 us at 6,001 dense ones (float32 MFMAs: 440, 122).
 //     A non-finite input makes its atom's results NaN.
 #include <cmath>
 #include <cstring>
@@ -52,6 +60,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // Read through a global-address-space pointer: a generic (flat) load would
 // also count against the LDS wait counter.
 typedef __attribute__((address_space(1))) const f32x4 gfloat4;
@@ -72,11 +81,17 @@ constexpr int kRad = 7;                // radial feature blocks of 16 (one per s
 enum { kF1, kF2, kF3, kA3, kA2, kA1, kPacks };
 constexpr int kPackK[kPacks] = {K0, N1, N2, N3, N2, N1};
 constexpr int kPackN[kPacks] = {N1, N2, N3, N2, N1, K0};
-constexpr int pack_first(int q) { return q == 0 ? 0 : pack_first(q - 1) + kPackK[q - 1] * kPackN[q - 1]; }   // elements
+constexpr int pack_first(int q) {   // fragments of 512 weights
+    return q == 0 ? 0 : pack_first(q - 1) + kPackK[q - 1] * kPackN[q - 1] / 512;
+}
 
 // planes of an operand: hi and lo float16 (FP32 form), or one bfloat16
 template <bool BF>
 constexpr int planes() { return BF ? 1 : 2; }
+// bytes of a packed fragment: two float16 and four bits a weight (FP32 form), or
+// one bfloat16
+template <bool BF>
+constexpr int frag_bytes() { return BF ? 1024 : 2048 + 256; }
 
 // CELU and its derivative, without branches.  FP32 form: with e = exp(min(v, 0)
 // / alpha), which is exactly 1 for v >= 0, CELU(v) = max(v, 0) + alpha (e - 1),
@@ -121,15 +136,22 @@ __host__ __device__ __forceinline__ Pow2 pow2_scale(float m) {
 // columns negated, and this sign goes into their scale, so that these columns
 // err upwards: those with an odd number of ones among the four low bits of
 // their index, a sequence that leaves no mean and no trend over the shells of a
-// feature block (with every other column negated, the error of a box's total
-// virial, a sum over atoms and features, had a mean of 6e-7 of it).
+// feature block.  (Over ten sets of weights, the networks' part of a box's
+// virial: 3.3e-8 of its atoms'; without the signs 1.1e-7; float32 MFMAs 6.3e-8.)
 template <bool BF>
 __host__ __device__ __forceinline__ float col_sign(int n) { return !BF && (0x6996 >> (n & 15) & 1) ? -1.f : 1.f; }
 
-// One operand fragment: 16 rows (or columns) x 32 k, per plane 8 values per lane
+// One operand fragment: 16 rows (or columns) x 32 k, per plane 8 values per
+// lane; of weights with the remainders (FP32 form)
 template <bool BF>
 struct Frag {
     u16x8 p[planes<BF>()];
+};
+template <bool BF>
+struct WFrag : Frag<BF> {};
+template <>
+struct WFrag<false> : Frag<false> {
+    unsigned r;
 };
 
 // Activation fragments of k-step ks (LDS planes `plane` elements apart, row stride ld)
@@ -155,9 +177,28 @@ __device__ __forceinline__ f32x4 mfma(u16x8 b, u16x8 a, f32x4 c) {
                                                       0, 0);
 }
 
+// The remainders of eight weights, from four bits each: of the remainder times
+// kRest, a power of two, a float16's exponent field f (2^(f - 15); 0: none), in
+// the order 0, 2, 4, 6, 1, 3, 5, 7 from the lowest bits, the odd ones negative
+constexpr float kRest = 512.f;
+__device__ __forceinline__ u16x8 remainders(unsigned w) {
+    constexpr unsigned field = 0x3c003c00u, odd = 0x80000000u;
+    const u32x4 r = {(w << 10 & field) | odd, (w << 6 & field) | odd, (w << 2 & field) | odd, (w >> 2 & field) | odd};
+    return __builtin_bit_cast(u16x8, __builtin_bit_cast(f16x8, r) * (_Float16)(1.f / kRest));
+}
+
 template <bool BF, int MB, int NCB, bool kAtoms = false>
-__device__ __forceinline__ void mfma_kstep(const Frag<BF> (&a)[MB], const Frag<BF> (&b)[NCB], f32x4 (&acc)[MB][NCB]) {
+__device__ __forceinline__ void mfma_kstep(const Frag<BF> (&a)[MB], const WFrag<BF> (&b)[NCB], f32x4 (&acc)[MB][NCB]) {
     constexpr int kProd = BF ? 1 : 3;
+    if constexpr (!BF) {
+#pragma unroll
+        for (int nb = 0; nb < NCB; ++nb) {
+            const u16x8 r = remainders(b[nb].r);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                acc[mb][nb] = kAtoms ? mfma<BF>(a[mb].p[0], r, acc[mb][nb]) : mfma<BF>(r, a[mb].p[0], acc[mb][nb]);
+        }
+    }
     constexpr int pb[3] = {BF ? 0 : 1, 0, 0}, pa[3] = {0, BF ? 0 : 1, 0};
 #pragma unroll
     for (int q = 0; q < kProd; ++q)
@@ -174,22 +215,24 @@ __device__ __forceinline__ void mfma_kstep(const Frag<BF> (&a)[MB], const Frag<B
 typedef __amdgpu_buffer_rsrc_t PackBuf;
 template <bool BF>
 __device__ __forceinline__ PackBuf pack_buf(const void* packs) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)packs, 0, pack_first(kPacks) * planes<BF>() * 2, 0x00027000);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)packs, 0, pack_first(kPacks) * frag_bytes<BF>(), 0x00027000);
 }
 
 // Weight fragments of the column blocks blk and k-step ks of pack q:
-// [block][k-step][plane][64 lanes][8]
+// [block][k-step][plane][64 lanes][8] (and the remainders' bits)
 template <bool BF, int Q, int NCB>
-__device__ __forceinline__ void load_b(PackBuf B, const int (&blk)[NCB], int ks, Frag<BF> (&b)[NCB]) {
+__device__ __forceinline__ void load_b(PackBuf B, const int (&blk)[NCB], int ks, WFrag<BF> (&b)[NCB]) {
     constexpr int NK = kPackK[Q] / KS;
     const int lane = 16 * lane_id();
 #pragma unroll
-    for (int nb = 0; nb < NCB; ++nb)
+    for (int nb = 0; nb < NCB; ++nb) {
+        const int at = (pack_first(Q) + blk[nb] * NK + ks) * frag_bytes<BF>();
 #pragma unroll
         for (int p = 0; p < planes<BF>(); ++p)
-            b[nb].p[p] = __builtin_bit_cast(
-                u16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                           B, lane + 1024 * p, (pack_first(Q) * 2 + (blk[nb] * NK + ks) * 1024) * planes<BF>(), 0));
+            b[nb].p[p] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane + 1024 * p, at, 0));
+        if constexpr (!BF)
+            b[nb].r = __builtin_amdgcn_raw_buffer_load_b32(B, lane / 4 + 2048, at, 0);
+    }
 }
 
 // Ring of weight-fragment registers: k-step t lives in slot t % RS and is
@@ -216,7 +259,7 @@ struct BPipe {
     static constexpr int NK = kPackK[Q] / KS;
     static constexpr int PD = ring_ahead<BF>(), RS = ring_slots<BF>();
     static_assert(NK >= PD, "");
-    Frag<BF> rb[RS][NCB];
+    WFrag<BF> rb[RS][NCB];
     int blk[NCB];
     // wave w's blocks w + NW i, or those of list
     __device__ __forceinline__ void start(PackBuf B, int w) {
@@ -618,12 +661,12 @@ __global__ __launch_bounds__(kThreads, TM > 32 ? 2 : 3) void k_mlp_fused(const F
         // is known at compile time
         constexpr int PD = ring_ahead<BF>(), RS = ring_turn<BF>();
         static_assert(CS % RS == 0, "a chunk holds whole ring turns");
-        Frag<BF> rb[RS][NC1];
+        WFrag<BF> rb[RS][NC1];
         int blk[NC1];
 #pragma unroll
         for (int nb = 0; nb < NC1; ++nb) blk[nb] = w + NW * nb;
         unsigned left_b = km;
-        auto loadB = [&](Frag<BF> (&d)[NC1]) { load_b<BF, kF1, NC1>(wb, blk, take(left_b), d); };
+        auto loadB = [&](WFrag<BF> (&d)[NC1]) { load_b<BF, kF1, NC1>(wb, blk, take(left_b), d); };
         if (nk > 0) {   // a tile of atoms without neighbours has no active k-step (h1 = CELU(b1))
             gload();
 #pragma unroll
@@ -877,8 +920,8 @@ __global__ __launch_bounds__(kThreads, TM > 32 ? 2 : 3) void k_mlp_fused(const F
 // form: each network's product has its own scales, and is added to the sum
 // in float32; BF16: one accumulation over K = 256 n_nets.
 template <bool BF, int TM, bool kDir>
-__global__ __launch_bounds__(kThreads, 2) void k_ens_adj1(const FusedArgs A, int n_nets, float inv_nets,
-                                                         float* E_atom_net, int n_atoms) {
+__global__ __launch_bounds__(kThreads, BF ? 2 : 3) void k_ens_adj1(const FusedArgs A, int n_nets, float inv_nets,
+                                                                  float* E_atom_net, int n_atoms) {
     constexpr int NG = 16 / NW;
     constexpr int NP = planes<BF>();
     constexpr int MB = TM / 16;
@@ -992,54 +1035,60 @@ static float host_f16_value(uint16_t h) {
 
 uint16_t host_bf16_bits(float f);
 
-// Packs B[k][n] (k < K, n < N, accessor) into MFMA fragment order:
-//   out[(((nb * K/32 + ks) * planes + p) * 64 + lane) * 8 + e]
-//     = plane p of B[32 ks + 8 (lane/16) + e][16 nb + lane%16]
-// (BF16: the rounded value; FP32 form: hi and lo float16 of s B times the
-// columns' signs).
+// Packs B[k][n] (k < K, n < N, accessor) into MFMA fragment order; fragment
+// nb K/32 + ks (column block nb, k-step ks) holds plane p at [p][lane][e]
+// (16-bit values), then the remainders' four bits each (remainders()) at [lane],
+// of B[32 ks + 8 (lane/16) + e][16 nb + lane%16] (BF16: the rounded value; FP32
+// form: hi and lo float16 of s B times the columns' signs).
 //
-// hi + lo holds 23 of a weight's 24 bits, so that for about one weight in
-// four lo lies halfway between two float16 numbers.  These errors are the same
-// for every atom and would add up in sums over atoms, so where an input of the
-// product is known to point along along[k] for most atoms, each such lo is
-// rounded to the side that keeps sum_k error[k][n] along[k] nearest zero.
+// hi + lo holds 23 of a weight's 24 bits: for one weight in four, what hi leaves
+// lies halfway between two float16 numbers.  The remainder, a power of two,
+// completes the weight: lo is the lower of the two at even e and the upper at
+// odd e, so that the remainders, of which an accumulator's last bits drop a
+// part, are as often negative as positive.  (Left out, these errors, the same
+// for every atom, made the mean error of a species' energies 6.1e-9 of their
+// terms over six sets of weights, the largest 1.7e-8; with the remainders
+// 4.4e-9 and 1.0e-8; float32 MFMAs 4.3e-9 and 1.3e-8.)
 template <typename F>
-static void pack_matrix(uint16_t* out, bool bf16, float s, int K, int N, const double* along, F B) {
+static void pack_matrix(char* out, bool bf16, float s, int K, int N, F B) {
     for (int n = 0; n < N; ++n) {
-        double off = 0.;
         for (int k = 0; k < K; ++k) {
             const float v = bf16 ? B(k, n) : B(k, n) * col_sign<false>(n);
-            const size_t step = (size_t)(n / 16) * (K / KS) + k / KS;
-            const int at = ((k % KS) / 8 * 16 + n % 16) * 8 + k % 8;
+            const size_t frag = (size_t)(n / 16) * (K / KS) + k / KS;
+            const int lane = (k % KS) / 8 * 16 + n % 16, e = k % 8;
             if (bf16) {
-                out[step * 512 + at] = host_bf16_bits(v);
+                ((uint16_t*)(out + frag * frag_bytes<true>()))[lane * 8 + e] = host_bf16_bits(v);
                 continue;
             }
+            uint16_t* planes = (uint16_t*)(out + frag * frag_bytes<false>());
             const uint16_t hi = host_f16_bits(v * s);
-            const float rest = v * s - host_f16_value(hi);
-            uint16_t lo = host_f16_bits(rest);
-            if (along) {
-                const double e0 = (double)host_f16_value(lo) - rest;
-                if (e0 != 0.) {
-                    const uint16_t other = fabs(host_f16_value(lo)) > fabs(rest) ? lo - 1 : lo + 1;
-                    const double e1 = (double)host_f16_value(other) - rest;
-                    const bool turn = e1 == -e0 && fabs(off + e1 * along[k]) < fabs(off + e0 * along[k]);
-                    if (turn) lo = other;
-                    off += (turn ? e1 : e0) * along[k];
+            const float left = v * s - host_f16_value(hi);
+            uint16_t lo = host_f16_bits(left);
+            if (host_f16_value(lo) != left) {
+                // the neighbour of left that leaves a remainder of e's sign
+                const bool above = host_f16_value(lo) > left, up = e & 1;
+                const uint16_t to = above == up ? lo : (lo & 0x8000u) ? (up ? lo - 1 : lo + 1) : (up ? lo + 1 : lo - 1);
+                const float rest = fabsf(left - host_f16_value(to)) * kRest;
+                if (rest >= 0x1p-14f && rest <= 1.f) {
+                    const int f = ilogbf(rest) + 15;
+                    if (ldexpf(1.f, f - 15) == rest) {
+                        lo = to;
+                        ((uint32_t*)(planes + 1024))[lane] |= (uint32_t)f << (4 * (e / 2) + 16 * (e & 1));
+                    }
                 }
             }
-            out[step * 1024 + at] = hi;
-            out[step * 1024 + 512 + at] = lo;
+            planes[lane * 8 + e] = hi;
+            planes[512 + lane * 8 + e] = lo;
         }
     }
 }
 
-// Builds the six packs of one species from row-major W_l [out][in] and the
-// head w4 (host); inv (FP32 form): 1 / the scale of each.  Returns bytes used
-// at dst (dst may be null to size).
+// Builds the six packs of one species from row-major W_l [out][in] (host) at
+// zeroed dst; inv: 1 / the scale of each.  Returns bytes used at dst (dst may be
+// null to size).
 size_t pack_fused_species(char* dst, float* inv, bool bf16, const float* W1, const float* W2, const float* W3,
-                          const float* w4, int n_in, int n3) {
-    const size_t unit = bf16 ? 2 : 4;
+                          int n_in, int n3) {
+    const size_t unit = bf16 ? frag_bytes<true>() : frag_bytes<false>();
     if (!dst) return pack_first(kPacks) * unit;
     // logical padded matrices: W1p [N1][K0], W2p [N2][N1], W3p [N3][N2] (rows >= n3 zero)
     auto w1 = [&](int o, int i) { return i >= 0 && i < n_in ? W1[(size_t)o * n_in + i] : 0.f; };
@@ -1051,22 +1100,10 @@ size_t pack_fused_species(char* dst, float* inv, bool bf16, const float* W1, con
         return m;
     };
     Pow2 sc[3] = {{1.f, 1.f}, {1.f, 1.f}, {1.f, 1.f}};
-    // The adjoint's inputs lie, for most atoms, near what CELU' = 1 everywhere
-    // gives: w4, W3^T w4, W2^T W3^T w4 (the mean over atoms of an organic box
-    // has a cosine of 0.93 to 0.98 with these in a randomly weighted network).
-    // Packed towards them, the mean over atoms of dE/dAEV's error against 64
-    // bits halves (hydrogens of that box: norm 1.1e-7 to 6.8e-8; float32 MFMAs:
-    // 1.6e-7).
-    double v3[N3] = {}, v2[N2] = {}, v1[N1] = {};
     if (!bf16) {
         sc[0] = pow2_scale(largest(W1, (size_t)N1 * n_in));
         sc[1] = pow2_scale(largest(W2, (size_t)N2 * N1));
         sc[2] = pow2_scale(largest(W3, (size_t)n3 * N2));
-        for (int o = 0; o < n3; ++o) v3[o] = w4[o];
-        for (int o = 0; o < n3; ++o)
-            for (int i = 0; i < N2; ++i) v2[i] += v3[o] * W3[(size_t)o * N2 + i];
-        for (int o = 0; o < N2; ++o)
-            for (int i = 0; i < N1; ++i) v1[i] += v2[o] * W2[(size_t)o * N1 + i];
     }
     for (int q = 0; q < kPacks; ++q) {
         auto B = [&](int k, int n) -> float {
@@ -1081,8 +1118,7 @@ size_t pack_fused_species(char* dst, float* inv, bool bf16, const float* W1, con
             }
         };
         const Pow2& c = sc[q < 3 ? q : 5 - q];
-        const double* along = bf16 || q < kA3 ? nullptr : q == kA3 ? v3 : q == kA2 ? v2 : v1;
-        pack_matrix((uint16_t*)(dst + pack_first(q) * unit), bf16, c.s, kPackK[q], kPackN[q], along, B);
+        pack_matrix(dst + pack_first(q) * unit, bf16, c.s, kPackK[q], kPackN[q], B);
         inv[q] = c.inv;
     }
     return pack_first(kPacks) * unit;

@@ -405,7 +405,7 @@ hipError_t launch_mlp_ensemble(const nnp_model* m, const MlpWs& W, const void* a
                                float* E_row, float* E_atomo, int n_atoms, void* d1_scratch, float* d1_inv,
                                float* E_net, float* E_atom_net, hipStream_t s);
 size_t pack_fused_species(char* dst, float* inv, bool bf16, const float* W1, const float* W2, const float* W3,
-                          const float* w4, int n_in, int n3);
+                          int n_in, int n3);
 uint16_t host_bf16_bits(float f);
 hipError_t launch_mlp_fused(const nnp_model* m, const MlpWs& W, const void* aev, float* g_out, bool direct,
                             float* E_row, float* E_atomo, int n_atoms, hipStream_t s);
