@@ -47,6 +47,31 @@ __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(
 __device__ __forceinline__ float hw_log2(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ float hw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The adjoint's distances, roots and cutoffs.  An error that is the same for
+// every pair adds up in a box's virial, where such errors were most of its
+// error: two roundings of pi / (2 pi Rc) 4.8e-8, v_sqrt_f32 1.2e-8 low in the
+// mean.  So the square root takes one Newton step (inv: the reciprocal), and the
+// cutoffs take turns, as v_cos_f32 and v_sin_f32 do, from r / (2 Rc) with the
+// factor in two parts: over ten sets of weights a box's virial errs by 6.8e-8 of
+// its atoms', before by 1.7e-7, for 1 % of the adjoint's time (306 and 309 us at
+// 99,999 atoms, 72.1 and 72.8 at 23,000 organic ones).
+__device__ __forceinline__ float root(float x, float& inv) {
+    const float s = hw_sqrt(x);
+    inv = hw_rcp(s);
+    return x > 0.f ? fmaf(fmaf(-s, s, x), 0.5f * inv, s) : s;
+}
+__device__ __forceinline__ float root(float x) {
+    float inv;
+    return root(x, inv);
+}
+__device__ __forceinline__ float cutoff_turns(float r, const CutoffTurns& c) { return fmaf(r, c.hi, r * c.lo); }
+__device__ __forceinline__ float cutoff_fc(float r, const CutoffTurns& c) {
+    return fmaf(0.5f, __builtin_amdgcn_cosf(cutoff_turns(r, c)), 0.5f);
+}
+__device__ __forceinline__ float cutoff_dfc(float r, const CutoffTurns& c) {
+    return c.slope * __builtin_amdgcn_sinf(cutoff_turns(r, c));
+}
+
 __device__ __forceinline__ int species_pair(int s, int t, int ns) {
     if (s > t) { int u = s; s = t; t = u; }
     return s * ns - (s * (s - 1)) / 2 + (t - s);
@@ -578,14 +603,14 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
     for (int q = 0; q < kQ; ++q) {
         r_[q] = 0.f;
         if (q >= nq) continue;   // wave-uniform: a group past the row's end
-        r_[q] = hw_sqrt(R.r2[q]);
+        r_[q] = root(R.r2[q]);
         if (pr_[q] >= 0) S.rl[pr_[q]] = make_float2(r_[q], __int_as_float(R.z[q]));
         if (pa_[q] >= 0) {
             const float r = r_[q];
             const float inv = r > 0.f ? hw_rcp(r) : 0.f;
             S.au[pa_[q]] = make_float4(R.vx[q] * inv, R.vy[q] * inv, R.vz[q] * inv, r);
-            S.afc[pa_[q]] = cutoff_fc(r, P.pi_rc_a);
-            S.adfc[pa_[q]] = -0.5f * P.pi_rc_a * __sinf(P.pi_rc_a * r);
+            S.afc[pa_[q]] = cutoff_fc(r, P.turns_a);
+            S.adfc[pa_[q]] = cutoff_dfc(r, P.turns_a);
             S.azs[pa_[q]] = R.z[q] | ((l + kWave * q) << 8);
         }
     }
@@ -617,8 +642,8 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
             a1 = fmaf(ge, d, a1);
             a2 += ge;
         }
-        const float fc = cutoff_fc(r, P.pi_rc_r);
-        const float dfc = -0.5f * P.pi_rc_r * __sinf(P.pi_rc_r * r);
+        const float fc = cutoff_fc(r, P.turns_r);
+        const float dfc = cutoff_dfc(r, P.turns_r);
         S.rl[m].x = P.pr * (-2.f * P.eta_r * fc * a1 + dfc * a2);
     }
     wave_sync();
@@ -660,7 +685,8 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
                 float c = A.x * B.x + A.y * B.y + A.z * B.z;
                 c = fminf(1.f, fmaxf(-1.f, c));
                 const float uu = P.cs * c;
-                const float sq = hw_sqrt(1.f - uu * uu);
+                float isq;
+                const float sq = root(1.f - uu * uu, isq);
                 const float rj = A.w, rk = B.w;
                 const float rbar = 0.5f * (rj + rk);
                 const float fj = S.afc[ja], fk = S.afc[ka];
@@ -686,7 +712,7 @@ __global__ __launch_bounds__(kWaves* kWave, kVir ? 4 : 5) void k_aev_bwd(
                 }
                 float Rz[kNa] = {0.f, 0.f, 0.f, 0.f};
                 float sum_c = 0.f;
-                const float us = uu * hw_rcp(sq);                 // u / sqrt(1 - u^2)
+                const float us = uu * isq;                        // u / sqrt(1 - u^2)
 #pragma unroll
                 for (int z = 0; z < kNz; ++z) {
                     // base^(zeta-1), of which base^zeta and its derivative

@@ -407,6 +407,12 @@ nnp_status nnp_model_create_ensemble(const nnp_aev_params* a, const nnp_mlp_para
     P.cs = a->cos_scale;
     P.pi_rc_r = (float)(M_PI / (double)a->rc_r);
     P.pi_rc_a = (float)(M_PI / (double)a->rc_a);
+    const auto turns = [](double rc) {
+        const float hi = (float)(0.5 / rc);
+        return CutoffTurns{hi, (float)(0.5 / rc - hi), (float)(-0.5 * M_PI / rc)};
+    };
+    P.turns_r = turns(a->rc_r);
+    P.turns_a = turns(a->rc_a);
     for (int k = 0; k < kNr; ++k) P.shf_r[k] = a->shf_r[k];
     for (int k = 0; k < kNa; ++k) P.shf_a[k] = a->shf_a[k];
     for (int k = 0; k < kNz; ++k) {

@@ -18,6 +18,11 @@ constexpr int kNa = 4;              // angular radial shells
 constexpr int kNz = 8;              // angle sections
 constexpr float kAccUnit = 9.648533212e-3f;   // eV / (A amu) -> A / fs^2
 
+// A cutoff's 1 / (2 Rc) as the sum of two floats, and -pi / (2 Rc)
+struct CutoffTurns {
+    float hi, lo, slope;
+};
+
 // AEV hyper-parameters as kernels see them (passed by value).
 struct AevConst {
     int ns;              // species
@@ -26,6 +31,7 @@ struct AevConst {
     int stride;          // dim rounded up to a multiple of 64
     float rc_r, eta_r, rc_a, eta_a, zeta, pr, cs;
     float pi_rc_r, pi_rc_a;   // pi / Rc
+    CutoffTurns turns_r, turns_a;
     float shf_r[kNr];
     float shf_a[kNa];
     float cos_z[kNz];
