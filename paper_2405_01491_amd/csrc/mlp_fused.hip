@@ -43,7 +43,8 @@
 //     (1.3e-7); over ten sets, a box's virial 3.3e-8 of its atoms' (6.3e-8).
 //     The fourth product takes a quarter more time: 184 and 226 us at 99,999
 //     water atoms, 57 and 72 us at 6,001 dense ones (float32 MFMAs: 440, 122).
-//     A non-finite input makes its atom's results NaN.
+//
+// A non-finite input makes its atom's results NaN, and no other atom's.
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -98,8 +99,9 @@ constexpr int frag_bytes() { return BF ? 1024 : 2048 + 256; }
 // of which one term is zero, and CELU'(v) = e.  BF16 form: the derivative from
 // the output, h > 0 ? 1 : 1 + h / alpha (its results are rounded to bfloat16,
 // so that the last bit of h decides some of them: the expressions stay as they
-// are).  CeluConst: alpha, 1 / alpha, and log2(e) / alpha as the sum of two
-// floats (one float's error, the same for every atom, would bias their sum).
+// are).  A NaN stays one (fminf would make it 0).  CeluConst: alpha, 1 / alpha,
+// and log2(e) / alpha as the sum of two positive floats (one float's error, the
+// same for every atom, would bias their sum; v = -inf gives e = 0).
 struct CeluConst {
     float a, ia, k_hi, k_lo;
 };
@@ -108,7 +110,7 @@ struct Celu {
 };
 template <bool BF>
 __device__ __forceinline__ Celu celu(float v, const CeluConst& c) {
-    const float x = fminf(v, 0.f);
+    const float x = v > 0.f ? 0.f : v;
     if constexpr (BF) {
         const float neg = c.a * (__expf(x * c.ia) - 1.f);
         const float h = v > 0.f ? v : neg;
@@ -1175,7 +1177,9 @@ FusedArgs fused_args(const nnp_model* m, const MlpWs& W, const void* aev, float*
     A.E_row = E_row;
     A.E_atomo = E_atomo;
     const double k = 1.4426950408889634 / (double)m->celu_alpha;
-    A.celu = {m->celu_alpha, 1.f / m->celu_alpha, (float)k, (float)(k - (double)(float)k)};
+    float k_hi = (float)k;
+    if ((double)k_hi >= k) k_hi = nextafterf(k_hi, 0.f);
+    A.celu = {m->celu_alpha, 1.f / m->celu_alpha, k_hi, (float)(k - (double)k_hi)};
     A.rows = W.rows_max;
     A.amask = W.amask;
     return A;
