@@ -354,9 +354,10 @@ __global__ __launch_bounds__(kWaves* kWave) void k_aev_fwd(
     const bool reverse = kPacked && (int)blockIdx.x >= n_fwd;
     const int i = ((int)blockIdx.x - (reverse ? n_fwd : 0)) * kWaves + w;
     if (i >= n) return;
-    // Fixed-stride rows just rebuilt: blocks after the features' (only then
-    // launched; gated like the rebuild) find the reverse index, which nothing
-    // here reads, once per unordered pair, by the row of its lower index.  In
+    // Fixed-stride rows just rebuilt: blocks after the features' find the
+    // reverse index, which nothing here reads, once per unordered pair, by the
+    // row of its lower index (launched with every call that keeps such an index;
+    // without a rebuild the gate ends them at once).  In
     // the features' own waves the search stood before everything else, up to
     // eight dependent reads (bisection) on a chip that few atoms leave idle;
     // beside them, us on a rebuild step, before and after: 23.8 -> 21.6 at

@@ -741,8 +741,13 @@ __global__ __launch_bounds__(W* kWave) void k_rows_cells(
 // entries: a row cut short by a capacity clamp stays in bounds), and the
 // reverse index: rev[p] of i -> j is the position of i in j's sorted staging
 // row.  An absent reverse (only a clamped or truncated list can lack one)
-// points the pair at itself and raises NNP_FLAG_REVERSE.
-template <bool kHalf>
+// points the pair at itself and raises NNP_FLAG_REVERSE.  Each row finds its
+// own slots, so that a pair listed on one side only is seen from that side (a
+// search of each pair from its lower row alone takes 72 us at 99,999 atoms and
+// leaves the upper row's slot unwritten).  kQuads: four lanes a row
+// (reverse_slots), else one lane a slot by bisection, which is shorter code and
+// a shorter search where the launch is latency (kQuadRows).
+template <bool kQuads>
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact(
     int n, const int32_t* __restrict__ row_count, const int32_t* __restrict__ stage_col,
     const int32_t* __restrict__ stage_sh, const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col,
@@ -765,10 +770,37 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact(
         shift[3 * p + 0] = (int8_t)(sh & 0xff);
         shift[3 * p + 1] = (int8_t)((sh >> 8) & 0xff);
         shift[3 * p + 2] = (int8_t)((sh >> 16) & 0xff);
+        if (kQuads) continue;
+        const int32_t* rj = stage_col + (size_t)j * kRowLds;
+        const int bj = row_ptr[j];
+        const int cj = min(row_count[j], row_ptr[j + 1] - bj);
+        int lo = 0, hi = cj;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (rj[mid] < i) lo = mid + 1; else hi = mid;
+        }
+        const bool found = lo < cj && rj[lo] == i;
+        rev[p] = found ? bj + lo : p;
+        if (!found) set_flag(flags, NNP_FLAG_REVERSE);
     }
-    const auto first = [&](int j) { return row_ptr[j]; };
-    const auto len = [&](int j) { return row_ptr[j + 1] - row_ptr[j]; };   // at most the row's count
-    if (reverse_slots<kHalf>(i, cnt, b, sc, stage_col, len, first, rev)) set_flag(flags, NNP_FLAG_REVERSE);
+    if (kQuads) {
+        const auto first = [&](int j) { return row_ptr[j]; };
+        const auto len = [&](int j) { return row_ptr[j + 1] - row_ptr[j]; };   // at most the row's count
+        if (reverse_slots<false>(i, cnt, b, sc, stage_col, len, first, rev)) set_flag(flags, NNP_FLAG_REVERSE);
+    }
+}
+
+// Rows from which k_compact searches with four lanes a row; us by bisection and
+// so: 5.3 and 6.3 at 1,500 water atoms, 5.9 and 6.5 at 3,000, 5.9 and 7.6 at 4,656
+// of molecules, 11.2 and 9.8 at 6,000, 31 and 24 at 23,000, 128 and 89 at 99,999
+// (468 and 366 there with rows of 150).
+constexpr int kQuadRows = 5000;
+
+void launch_compact(int n, const int32_t* row_count, const int32_t* stage_col, const int32_t* stage_sh,
+                    const nnp_nlist* nl, const int32_t* gate, unsigned* flags, hipStream_t s) {
+    const auto run = n >= kQuadRows ? k_compact<true> : k_compact<false>;
+    run<<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(n, row_count, stage_col, stage_sh, nl->row_ptr,
+                                                                     nl->col, nl->shift, nl->rev, gate, flags);
 }
 
 __global__ void k_fill_gated(int32_t* p, long n, int32_t v, const int32_t* gate) {
@@ -1163,9 +1195,7 @@ nnp_status build_neighbors(nnp_model* model, int32_t n, const float* pos, const 
         nl->n_atoms = n;
         nl->r_list = r_list;
         nl->n_pairs = -1;
-        if (n > 0)
-            k_compact<false><<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(   // cut rows: not symmetric
-                n, row_count, stage_col, stage_sh, nl->row_ptr, nl->col, nl->shift, nl->rev, gate, flags);
+        if (n > 0) launch_compact(n, row_count, stage_col, stage_sh, nl, gate, flags, s);
         prof_end(model, NNP_STAGE_NEIGHBORS, s);
         return hipGetLastError() == hipSuccess ? NNP_OK : NNP_E_HIP;
     }
@@ -1185,9 +1215,7 @@ nnp_status build_neighbors(nnp_model* model, int32_t n, const float* pos, const 
         return NNP_E_ARG;
     }
     if (total > nl->capacity || total > 0x7fffffffLL) return NNP_E_CAPACITY;
-    if (n > 0 && total > 0)
-        k_compact<true><<<ceil_div(n, kRowsPerBlock), kRowsPerBlock * kWave, 0, s>>>(
-            n, row_count, stage_col, stage_sh, nl->row_ptr, nl->col, nl->shift, nl->rev, nullptr, flags);
+    if (n > 0 && total > 0) launch_compact(n, row_count, stage_col, stage_sh, nl, nullptr, flags, s);
     prof_end(model, NNP_STAGE_NEIGHBORS, s);
     return hipGetLastError() == hipSuccess ? NNP_OK : NNP_E_HIP;
 }

@@ -295,15 +295,16 @@ __device__ __forceinline__ float3 gather_row_force(const RowsView& rows, const i
 // NNP_MAX_ROW j with len(j) entries, its slots from first(j).  Four lanes
 // search one row: each reads the last entry of one of its first four 16-entry
 // blocks, which tells i's block, then four of that block's entries, and the
-// lane that finds i writes (rows of more than 64 entries go on in steps of
-// 64).  Two dependent reads where a bisection by one lane has six to eight, and
-// a third of the instructions of sixteen lanes reading 64 entries at once:
-// k_compact at 99,999 atoms 128 us (bisection), 95 (sixteen lanes), 74; at
-// 1,500 atoms, where the launch is latency and instruction fetch, 5.5 and 6.2
-// (three or four times kRows at once: 5.8-6.3, and 70-77 at 99,999).
+// lane that finds i writes; beyond a row's first 64 entries the search goes on
+// block by block, one dependent read each.  Two dependent reads within those 64
+// where a bisection by one lane has six to eight, and a third of the
+// instructions of sixteen lanes reading 64 entries at once.
 // kHalf: only the neighbours j > i, both slots written, in lists that are
-// symmetric; else each row writes its own slots.  A neighbour without i leaves
-// the slot pointing at itself.  Returns whether that occurred on this lane.
+// symmetric but for rows emptied because they overflowed (k_aev_fwd's rebuilt
+// rows: the MD engine zeroes its slots once, a served request has too few atoms
+// to overflow one); else each row writes its own slots (k_compact, which holds
+// the times).  A neighbour without i leaves the slot pointing at itself.
+// Returns whether that occurred on this lane.
 template <bool kHalf, typename Len, typename First>
 __device__ __forceinline__ bool reverse_slots(int i, int cnt, int b, const int32_t* __restrict__ mine,
                                               const int32_t* __restrict__ cols, Len len, First first,
