@@ -705,7 +705,7 @@ nnp_status nnp_mlp(nnp_model* m, int32_t n, const int32_t* species, const float*
     const bool fused = m->fused && (!m->force_unfused || m->n_nets > 1);
     const bool bfa = fused && m->precision == NNP_BF16_MLP;   // the fused BF16 kernels' grouped rows are bf16
     // The fused kernels read and write the caller's rows where they are (the
-    // copies into and out of groups took 18 of 150 us at 6,001 atoms), unless
+    // copies into and out of groups took 18 of 87 us at 6,001 atoms), unless
     // their 16-byte loads would not be aligned, or a tile's gradients would
     // fall on features that another tile has yet to read.
     const size_t len = (size_t)n * m->aev.stride;

@@ -41,8 +41,9 @@
 //     species' energies 4.4e-9 (4.3e-9; largest 1.0e-8, 1.3e-8), a box's energy
 //     3.0e-9 (3.2e-9), dE/dAEV 3.0e-7 (4.7e-7), its sum over a box 0.7e-7
 //     (1.3e-7); over ten sets, a box's virial 3.3e-8 of its atoms' (6.3e-8).
-//     The fourth product takes a quarter more time: 184 and 226 us at 99,999
-//     water atoms, 57 and 72 us at 6,001 dense ones (float32 MFMAs: 440, 122).
+//     The fourth product takes a fifth to a quarter more time: 184 and 220 us
+//     at 99,999 water atoms, 57 and 71 us at 6,001 dense ones (float32 MFMAs:
+//     440, 122).
 //
 // A non-finite input makes its atom's results NaN, and no other atom's.
 #include <cmath>
@@ -180,13 +181,20 @@ __device__ __forceinline__ f32x4 mfma(u16x8 b, u16x8 a, f32x4 c) {
 }
 
 // The remainders of eight weights, from four bits each: of the remainder times
-// kRest, a power of two, a float16's exponent field f (2^(f - 15); 0: none), in
-// the order 0, 2, 4, 6, 1, 3, 5, 7 from the lowest bits, the odd ones negative
+// kRest, a power of two, a float16's exponent field f (2^(f - 15); 0: none).
+// Element e's lies at rest_bit(e) (past bit 31 it goes on at bit 0), where a
+// rotation brings each pair's fields into place; the odd ones are negative,
+// which the scaling back adds.  Eleven operations a fragment; with shifts, and
+// the odd signs set apart, sixteen (99,999 water atoms: 228 us, now 220).
 constexpr float kRest = 512.f;
+constexpr int rest_bit(int e) { return 10 + 16 * (e & 1) + 4 * (e / 2); }
 __device__ __forceinline__ u16x8 remainders(unsigned w) {
-    constexpr unsigned field = 0x3c003c00u, odd = 0x80000000u;
-    const u32x4 r = {(w << 10 & field) | odd, (w << 6 & field) | odd, (w << 2 & field) | odd, (w >> 2 & field) | odd};
-    return __builtin_bit_cast(u16x8, __builtin_bit_cast(f16x8, r) * (_Float16)(1.f / kRest));
+    constexpr unsigned field = 0x3c003c00u;
+    const u32x4 r = {w & field, __builtin_amdgcn_alignbit(w, w, 4) & field, __builtin_amdgcn_alignbit(w, w, 8) & field,
+                     __builtin_amdgcn_alignbit(w, w, 12) & field};
+    constexpr _Float16 c = (_Float16)(1.f / kRest);
+    constexpr f16x8 back = {c, -c, c, -c, c, -c, c, -c};
+    return __builtin_bit_cast(u16x8, __builtin_bit_cast(f16x8, r) * back);
 }
 
 template <bool BF, int MB, int NCB, bool kAtoms = false>
@@ -1075,7 +1083,8 @@ static void pack_matrix(char* out, bool bf16, float s, int K, int N, F B) {
                     const int f = ilogbf(rest) + 15;
                     if (ldexpf(1.f, f - 15) == rest) {
                         lo = to;
-                        ((uint32_t*)(planes + 1024))[lane] |= (uint32_t)f << (4 * (e / 2) + 16 * (e & 1));
+                        const uint64_t bits = (uint64_t)f << rest_bit(e);
+                        ((uint32_t*)(planes + 1024))[lane] |= (uint32_t)(bits | bits >> 32);
                     }
                 }
             }
@@ -1154,11 +1163,15 @@ void fused_net_entry(void* out, int ns, const char* const* packs, const float (*
 namespace {
 
 // Tile height.  A tile streams its species' whole weight packs whatever its
-// height, so 32 rows are the rule as soon as 16-row tiles would outnumber the
-// CUs (FP32, 4,500 water atoms: 24.5 us with 16 rows, 21.3 with 32; 6,001
-// organic ones, dense: 64 and 52); below that a tile is alone on its CU, and
-// the shorter one ends sooner (a 19-atom molecule: 16.9 and 20.5 us).  The
-// BF16 form keeps its 12 Ki atoms, and its ensemble takes 64 rows from 48 Ki
+// height, so 32 rows are the rule as soon as one network's 16-row tiles would
+// outnumber the CUs; below that a tile is alone on its CU, and the shorter one
+// ends sooner.  FP32, us with 16 and with 32 rows: a 19-atom molecule 31 and 42
+// (on an idle card), 3,000 water atoms 22.1 and 26.3, dense organic ones 54 and
+// 63; 4,500 27.3 and 26.5, 70 and 67; 9,000 38 and 36, 103 and 96.  An
+// ensemble's grid holds its networks' tiles side by side, so that 32 rows would
+// pay from fewer atoms (eight networks: 77 and 84 at 900 water atoms, 119 and 114
+// at 3,000; organic 133 and 114, 255 and 188); its line is the single network's.
+// The BF16 form keeps its 12 Ki atoms, and its ensemble takes 64 rows from 48 Ki
 // atoms, where the first-layer adjoint over all networks gains from it.
 int fused_tile_rows(int n_atoms, bool bf, bool ens) {
     if (!bf) return n_atoms >= 4096 ? 32 : 16;
