@@ -445,6 +445,16 @@ def serving_bench(model, duration_s=5.0, warmup_s=1.0, rate=2000.0, pool=600, pl
     return main
 
 
+def mlp_products(precision, fused):
+    """How the networks' matrix products are formed."""
+    if precision == "bf16":
+        return "bfloat16 operands, float32 accumulation"
+    if not fused:
+        return "float32"
+    return ("float16 parts of scaled float32 operands (weights in full, activations 22 to 24 bits), "
+            "float32 accumulation")
+
+
 METRIC = "energy+force atom-steps/s at 1 MI355X (FP32 vs BF16-MLP); p50/p99 request latency"
 
 
@@ -547,7 +557,9 @@ def main():
             "metric": METRIC, "value": sv["atoms_per_s"], "unit": "atom-steps/s", "n_gpus": 1,
             "steps": sv["requests"], "warmup": 0, "ms_per_step": sv["p50_ms"], "higher_is_better": True,
             "scaling": "weak", "vs_baseline": None, "dtype": "f32" if args.precision == "fp32" else "f32+bf16(mlp)",
-            "data": "synthetic", "config": {"workload": sv["workload"]}, "serving": sv}))
+            "data": "synthetic", "config": {"workload": sv["workload"],
+                                            "mlp_products": mlp_products(args.precision, model.fused_mlp)},
+            "serving": sv}))
         return
     w = synthetic.workload(args.config)
     precision = args.precision
@@ -626,7 +638,8 @@ def main():
         "dtype": "f32" if precision == "fp32" else "f32+bf16(mlp)", "data": "synthetic",
         "config": {"workload": workload + ("; ensemble of %d networks" % args.nets if args.nets > 1 else ""),
                    "n_atoms": N, "precision": precision, "skin_A": skin, "rebuild_every": every,
-                   "list_pairs": n_pairs, "networks": args.nets},
+                   "list_pairs": n_pairs, "networks": args.nets,
+                   "mlp_products": mlp_products(precision, model.fused_mlp)},
         "stages_ms_per_step_warmup": {k: round(ms / warm_steps, 5) for k, (ms, cnt) in warm.items()},
         "roofline": roof,
     }
@@ -650,7 +663,8 @@ def main():
             nnp.nnp_energy_forces(om, pos, sp, None, 1, w.box, nl2, out=out2)
         torch.cuda.synchronize()
         tb = (time.perf_counter() - ta) / args.steps
-        form = {"value": N / tb, "ms_per_step": 1e3 * tb, "dtype": "f32" if other == "fp32" else "f32+bf16(mlp)"}
+        form = {"value": N / tb, "ms_per_step": 1e3 * tb, "dtype": "f32" if other == "fp32" else "f32+bf16(mlp)",
+                "mlp_products": mlp_products(other, model.fused_mlp)}
     result["forms"] = {precision: {"value": value, "ms_per_step": result["ms_per_step"], "dtype": result["dtype"]},
                        other: form}
     models[other] = om
